@@ -172,6 +172,28 @@ def test_cluster_random_points_with_long_chains(torch_dev):
     np.testing.assert_array_equal(rep, rep_o)     # same order: same indices
 
 
+@pytest.mark.parametrize("n", [1, 2, 33, 600])
+@pytest.mark.parametrize("eps", [1.0, 3.0])
+def test_cluster_across_bitmap_words(torch_dev, n, eps):
+    """Hits whose cells lie around a change of bitmap word (64 cells of side
+    eps in x) and around 0 in y, u and v: every hit's representative index is
+    the oracle's."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    rng = np.random.default_rng(68 + n)
+    vel = rng.uniform(-6.0, 6.0, (40, 2))
+    xs = np.abs(rng.choice([0, 63, 64, 128], n) * int(eps) + rng.integers(-4, 5, n))
+    ys, js = rng.integers(0, 9, n), rng.integers(0, 40, n)
+    key = np.unique(np.stack([ys, xs, js], 1), axis=0)           # distinct trajectories
+    ys, xs, js = key[:, 0], key[:, 1], key[:, 2]
+    nu32 = rng.choice(np.array([10.0, 11.5, 12.0], dtype=np.float32), ys.size)
+    rep_o, _ = oc.cluster(xs, ys, js, nu32, vel, 0.4, eps)
+    _say(f"case cluster words: {ys.size} hits eps={eps}")
+    d = _upload_hits(torch, _oracle_records(ys, xs, js, nu32))
+    rep = lib.cluster_hits(d, ys.size, vel, 0.4, eps).cpu().numpy()
+    np.testing.assert_array_equal(rep, rep_o)
+
+
 @pytest.mark.parametrize("n,eps,s", [(200_000, 4.0, 2.24), (300_000, 2.0, 0.5)])
 def test_cluster_many_hits_against_sparse_oracle(torch_dev, n, eps, s):
     """Hundreds of thousands of hits (survey-sized frame and velocity grid,
