@@ -447,7 +447,8 @@ def run_search(img, var, mask, t, psf, vel, k, k_cand=None, stream=None, lp=None
     if lp is None:
         planes = make_psi_phi(img, var, mask, psf, stream=stream)
         cand = search(planes, t, vel, k_cand, stream=stream)
-        res = topk(cand, k, img.shape[0], stream=stream)
+        # Every candidate kept: ordered in place, without a second list.
+        res = topk(cand, k, img.shape[0], out=cand if k == k_cand else None, stream=stream)
         return planes, res
     planes, lp_planes, scale = make_psi_phi(img, var, mask, psf, stream=stream, lp=lp)
     n, h, w = img.shape
