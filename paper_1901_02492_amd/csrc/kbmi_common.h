@@ -52,12 +52,38 @@ kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_sc
                            hipStream_t s);
 
 // One displacement on the device: floor(v * tau + 0.5) as a separate IEEE
-// double multiply, add and floor (no contraction), clamped to [-lim, lim],
-// which rounds exactly as the host table does.
-__device__ inline int displacement(double v, double tau, int lim) {
+// double multiply, add and floor (no contraction), which rounds exactly as
+// the host table does.  The conversion saturates to the int32 range.
+__device__ inline int32_t displacement(double v, double tau) {
 #pragma clang fp contract(off)
     const double f = floor(v * tau + 0.5);
-    return (int)fmin(fmax(f, -(double)lim), (double)lim);
+    int32_t d;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(d) : "v"(f));
+    return d;
+}
+
+// The pixel (index in its image) that start pixel (x0, y0) reaches at tau; ok
+// says whether it is in the frame (index 0 if not).  Coordinates are added in
+// 32 bits without a clamp: frames have at most 2^30 rows and 2^27 columns, so
+// a saturated displacement lands outside [0, 2^31) or beyond the frame.  The
+// FP64 and 64-bit integer instructions here are most of what the kernels that
+// gather along candidates issue per image, hence no clamp and one wide
+// multiply: 18 vector instructions for 40.  A step of 9 x 613 x 1187, 260
+// velocities in bf16, re-scoring 52 a pixel: 3.00 -> 2.69 ms.
+__device__ inline uint64_t displaced_pixel(double2 v, double tau, int x0, int y0, int h, int w,
+                                           bool &ok) {
+    const uint32_t x = (uint32_t)x0 + (uint32_t)displacement(v.x, tau);
+    const uint32_t y = (uint32_t)y0 + (uint32_t)displacement(v.y, tau);
+    ok = y < (uint32_t)h && x < (uint32_t)w;
+    const uint64_t at = (uint64_t)y * (uint32_t)w + x;
+    return ok ? at : 0;
+}
+
+// q / k for 0 <= q < 4096 and k >= 1, inv_k = 1.f / k: the quotient's distance
+// from an integer above it is at least 1 / k, so half of that (q + 0.5)
+// absorbs the rounding.
+__device__ inline int small_quotient(int q, float inv_k) {
+    return (int)(((float)q + 0.5f) * inv_k);
 }
 
 }  // namespace kbmi

@@ -41,37 +41,34 @@ constexpr int LC_MAXQ = (LC_PAIRS + GR_THREADS - 1) / GR_THREADS;   // pairs per
 constexpr int LC_PX = 64;                            // start pixels per grouped tile, at most
 static_assert(LC_THREADS == GR_THREADS, "the grouped filter uses the shared grouping");
 
-// The light curve of candidate (start pixel p, velocity index j; an index
-// outside [0, n_vel) has no observation) into v; returns the observed images'
-// bits.  Every image's load is issued before any is used (an out-of-frame or
-// missing term reads pixel 0 and is then replaced by +0), so the loads of a
-// light curve are in flight together.
+// The light curve of the candidate at start pixel (x0, y0) with velocity
+// index j (an index outside [0, n_vel) has no observation) into v; returns the
+// observed images' bits.  Every image's load is issued before any is used (an
+// out-of-frame or missing term reads a pixel that is then not observed), so
+// the loads of a light curve are in flight together.
 template <int NB>
-__device__ __forceinline__ uint64_t gather_light_curve(int64_t p, int j, int h, int w, int n_img,
+__device__ __forceinline__ uint64_t gather_light_curve(int x0, int y0, int j, int h, int w,
+                                                       int n_img,
                                                        const float2 *__restrict__ planes,
                                                        const double *__restrict__ tau,
                                                        const double2 *__restrict__ vels,
                                                        int n_vel, float2 (&v)[NB]) {
     const bool has = j >= 0 && j < n_vel;
     const double2 vj = vels[has ? j : 0];
-    const int y0 = (int)(p / w), x0 = (int)(p - (int64_t)y0 * w);
+    const size_t image = (size_t)h * (size_t)w;
     bool ok[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        const double ti = tau[i < n_img ? i : 0];
-        const int y = y0 + displacement(vj.y, ti, h);
-        const int x = x0 + displacement(vj.x, ti, w);
-        ok[i] = has && i < n_img && (unsigned)y < (unsigned)h && (unsigned)x < (unsigned)w;
-        const size_t at = ok[i] ? ((size_t)i * h + y) * (size_t)w + x : 0;
-        v[i] = planes[at];
+        const int ii = i < n_img ? i : 0;
+        const uint64_t at = displaced_pixel(vj, tau[ii], x0, y0, h, w, ok[i]);
+        ok[i] = ok[i] && has && i < n_img;
+        v[i] = (planes + (size_t)ii * image)[at];
     }
     uint64_t obs = 0;   // bit i: image i observes the trajectory
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        if (!ok[i]) v[i] = make_float2(0.f, 0.f);
+    for (int i = 0; i < NB; ++i)
         // Validity is carried by phi's bits: invalid pixels hold +0.
-        if (__float_as_uint(v[i].y) != 0u) obs |= uint64_t(1) << i;
-    }
+        if (ok[i] && __float_as_uint(v[i].y) != 0u) obs |= uint64_t(1) << i;
     return obs;
 }
 
@@ -205,9 +202,11 @@ __global__ __launch_bounds__(LC_THREADS) void lightcurve_kernel(
     float *__restrict__ alpha, int16_t *__restrict__ nobs, uint64_t *__restrict__ rejected) {
     const int64_t c = (int64_t)blockIdx.x * LC_THREADS + threadIdx.x;
     if (c >= ncand) return;
+    const int64_t p = c / k, y0 = p / w;
     float2 v[NB];
     const uint64_t obs =
-        gather_light_curve<NB>(c / k, cand_vel[c], h, w, n_img, planes, tau, vels, n_vel, v);
+        gather_light_curve<NB>((int)(p - y0 * w), (int)y0, cand_vel[c], h, w, n_img, planes, tau,
+                               vels, n_vel, v);
     uint64_t keep = obs;
     for (;;) {   // at most popcount(obs) + 1 rounds
         int worst;
@@ -289,6 +288,7 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
             s_no[qq] = 0;
             if (rejected) rejected[c0 + qq] = 0;
         }
+    const float inv_k = 1.f / (float)k;
     int n_items = n_sorted;
 #pragma unroll 1
     for (int pass = 0; n_items > 0; ++pass) {
@@ -309,8 +309,9 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
                 dropped = s_ord[qq];
             }
             float2 v[NB];
-            const uint64_t obs = gather_light_curve<NB>(p0 + qq / k, s_vj[qq], h, w, n_img,
-                                                        planes, tau, vels, n_vel, v);
+            const uint64_t obs = gather_light_curve<NB>(ct * pt + small_quotient(qq, inv_k),
+                                                        (int)row, s_vj[qq], h, w, n_img, planes,
+                                                        tau, vels, n_vel, v);
             uint64_t keep = obs & ~dropped;
             bool queued = false;
             for (;;) {   // at most popcount(obs) + 1 rounds

@@ -21,6 +21,7 @@
 #include <cstdint>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "kbmi_common.h"
@@ -381,35 +382,39 @@ __global__ __launch_bounds__(TK_THREADS) void topk_rescore_kernel(
     for (int q = t; q < np; q += TK_THREADS)
         if (s_vj[q] < 0) s_key[q] = 0ull;
 
-    // Score the pairs in velocity-grouped order.
+    // Score the pairs in velocity-grouped order, eight images' gathers in
+    // flight; the images beyond a multiple of eight go in groups of 4, 2, 1.
+    const float inv_k = 1.f / (float)k_cand;
+    const size_t image = (size_t)h * (size_t)w;
     for (int pos = t; pos < n_sorted; pos += TK_THREADS) {
         const int q = s_ord[pos];
         const int j = s_vj[q];
-        const int lp = q / k_cand;
-        const int64_t p = p0 + lp;
-        const int y0 = (int)(p / w), x0 = (int)(p - (int64_t)y0 * w);
+        const int x0 = ct * RS_PX + small_quotient(q, inv_k);
         const double2 vj = vels[j];
         float P = 0.f, F = 0.f;
         uint32_t c = 0;
-        for (int i0 = 0; i0 < n_img; i0 += 8) {
-            float2 v[8];
+        auto add_images = [&](auto count, int i0) {
+            constexpr int B = decltype(count)::value;
+            float2 v[B];
+            bool ok[B];
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int i = i0 + b;
-                const double ti = tau[i < n_img ? i : 0];
-                const int y = y0 + displacement(vj.y, ti, h), x = x0 + displacement(vj.x, ti, w);
-                const bool ok = i < n_img && (unsigned)y < (unsigned)h && (unsigned)x < (unsigned)w;
-                const size_t idx = ok ? ((size_t)i * h + y) * (size_t)w + x : 0;
-                const float2 raw = planes[idx];
-                v[b] = ok ? raw : make_float2(0.f, 0.f);
+            for (int b = 0; b < B; ++b) {
+                const uint64_t at = displaced_pixel(vj, tau[i0 + b], x0, (int)row, h, w, ok[b]);
+                v[b] = (planes + (size_t)(i0 + b) * image)[at];
             }
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
+            for (int b = 0; b < B; ++b) {
+                if (!ok[b]) v[b] = make_float2(0.f, 0.f);
                 P += v[b].x;
                 F += v[b].y;
                 c += __float_as_uint(v[b].y) != 0u;
             }
-        }
+        };
+        int i0 = 0;
+        for (; i0 + 8 <= n_img; i0 += 8) add_images(std::integral_constant<int, 8>{}, i0);
+        if (n_img & 4) add_images(std::integral_constant<int, 4>{}, i0), i0 += 4;
+        if (n_img & 2) add_images(std::integral_constant<int, 2>{}, i0), i0 += 2;
+        if (n_img & 1) add_images(std::integral_constant<int, 1>{}, i0);
         const float r = inv_sqrt_phi(F);
         const float v_nu = score_nu(P, F, r);
         s_key[q] = make_key(v_nu, j, c);
@@ -423,7 +428,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_rescore_kernel(
     for (int r = 0; r < RS_MAXQ; ++r) {
         const int q = t + r * TK_THREADS;
         if (q < np) {
-            const int lp = q / k_cand, s = q - lp * k_cand;
+            const int lp = small_quotient(q, inv_k), s = q - lp * k_cand;
             const uint64_t key = s_key[q];
             const uint64_t *pk = s_key + lp * k_cand;
             int rank = 0;

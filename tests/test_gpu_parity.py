@@ -493,6 +493,30 @@ def test_rescore_of_plain_candidates_equals_topk(torch_dev, case):
         assert np.array_equal(fg[rest].view(np.uint8), ff[rest].view(np.uint8))
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 25])
+def test_rescore_of_any_image_count_and_far_velocities(torch_dev, n):
+    """Every remainder of the re-score's image groups, with velocities whose
+    displacements leave the frame by a little, by more than 2^31 pixels and by
+    more than a double holds as an integer: bit for bit the search's values."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    h, w, kc = 9, 67, 11
+    s = synth.random_stack(86, n=n, h=h, w=w, n_vel=40, k=kc, psf_size=5, vmax=60)
+    vel = s.vel.copy()
+    vel[1::5] *= 1e9
+    vel[3::5] *= 1e200
+    _say(f"case rescore remainder N={n}")
+    dev = torch.device("cuda:0")
+    img, var, mask = (torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask))
+    planes = lib.make_psi_phi(img, var, mask, s.psf)
+    cand = lib.search(planes, s.t, vel, kc)
+    plain = lib.topk(cand, kc, n)
+    again = lib.topk(cand, kc, n, rescore=(planes, s.t, vel, None))
+    torch.cuda.synchronize()
+    for a, b in zip(parity.to_numpy(plain), parity.to_numpy(again)):
+        assert np.ascontiguousarray(a).tobytes() == np.ascontiguousarray(b).tobytes()
+
+
 LP_BAND = {"f16": 1e-2, "bf16": 8e-2}   # nu band for near-ties after 16-bit pre-selection
 
 
