@@ -94,6 +94,12 @@ __device__ __forceinline__ double quotient(double a, double d, double ds, double
     const double rem = __builtin_fma(-ds, m, ns);
     return __builtin_amdgcn_div_fixup(__builtin_amdgcn_div_fmas(rem, r, m, flag), d, a);
 }
+// A quotient that needs neither scaling nor fix-up, r refined from d itself.
+__device__ __forceinline__ double plain_quotient(double a, double d, double r) {
+    const double m = a * r;
+    const double rem = __builtin_fma(-d, m, a);
+    return __builtin_fma(rem, r, m);
+}
 __device__ __forceinline__ void divide_pair(double &J, double &H, double d) {
     bool unused;
     const double dsj = __builtin_amdgcn_div_scale(J, d, false, &unused);
@@ -108,13 +114,39 @@ __device__ __forceinline__ void divide_pair(double &J, double &H, double d) {
     H = quotient(H, d, dsh, rh);
 }
 
-// One round of the filter over the kept observations: the largest squared
-// standardised residual (-1 if none is kept) and, in `worst`, its image (the
-// lowest among equal values).
+// Whether a light curve's divisions can leave out the scaling and the fix-up
+// of the hardware's sequence: no phi is negative or -0 and no term exceeds
+// 2^100 (an unobserved image's are the pair its gather read), and
+// q_span = 64 q (tau_last - tau_first) times the largest phi is at most 2^14
+// (times never decrease; the host passes NaN for cuts below 2^-900, where
+// residuals that round in the subnormal range decide).  Then J >= 0
+// throughout, so every divisor d = 1 + s J is in [1, 2^14 + 1]; the product of
+// at most 63 of them, their s adding up to the span, is below 2^505; |H|, once
+// nonzero, is at least 2^-149 (a float) or 2^-53 of that (cancelled against a
+// float) before it is divided, so J and H stay in {0} or [2^-710, 2^107]: no
+// operand is one that the sequence would scale, and no quotient is a special
+// case.  H is never -0 (sums that cancel give +0); a NaN gives NaN either way.
 template <int NB>
-__device__ __forceinline__ double filter_round(const float2 (&v)[NB], uint64_t keep,
-                                               const double *__restrict__ tau, double q,
-                                               int &worst) {
+__device__ __forceinline__ bool plain_divisions(const float2 (&v)[NB], float q_span) {
+    float top_psi = 0.f, top_phi = 0.f;
+    uint32_t sign = 0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        top_psi = fmaxf(top_psi, fabsf(v[i].x));
+        top_phi = fmaxf(top_phi, v[i].y);
+        sign |= __float_as_uint(v[i].y);
+    }
+    return (int32_t)sign >= 0 && top_psi <= 0x1p100f && top_phi <= 0x1p100f &&
+           q_span * top_phi <= 0x1p14f;
+}
+
+// One round of the filter over the kept observations: whether the largest
+// squared standardised residual exceeds c2 and, in `worst`, its image then
+// (the lowest among equal values).
+template <int NB>
+__device__ __forceinline__ bool filter_round_exact(const float2 (&v)[NB], uint64_t keep,
+                                                   const double *__restrict__ tau, double q,
+                                                   double c2, int &worst) {
 #pragma clang fp contract(off)
     const bool walk = q > 0.0;
     double Jf[NB], Hf[NB];
@@ -167,7 +199,97 @@ __device__ __forceinline__ double filter_round(const float2 (&v)[NB], uint64_t k
             seen = true;
         }
     }
-    return rmax;
+    return rmax > c2;
+}
+
+// The same round where plain_divisions holds.  Double-precision issue bounds
+// it: per image two divisions of a pair and one residual.
+//   - A pair's division is the exact round's refined reciprocal and quotient
+//     steps without the scaling and fix-up around them, which would change
+//     nothing (11 instructions for 21).  The first kept image's prediction
+//     divides 0 by 1, which leaves 0, so it needs no branch of its own.
+//   - The residuals are compared as N rcp(D), whose relative error is below
+//     2^-22 (the reciprocal instruction is good to 2^29 units in the last
+//     place), and only where they could exceed c2.  `close` says that an order
+//     or the cut itself lies within 2^-17 of a residual: such a light curve's
+//     round is repeated with the exact quotients.
+// The decisions are those of the exact quotients.  15 x 1024^2, 50 candidates a
+// pixel: 2281 vector instructions a candidate with the exact rounds alone, 1803
+// now; a call 4.21 ms, 4.00 with displaced_pixel, 3.65 with this round.
+template <int NB>
+__device__ __forceinline__ bool filter_round_plain(const float2 (&v)[NB], uint64_t keep,
+                                                   int n_img, const double *__restrict__ tau,
+                                                   double q, double c2, int &worst, bool &close) {
+#pragma clang fp contract(off)
+    const bool walk = q > 0.0;
+    // The times are fetched together here, not one by one where each is used.
+    double t[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        t[i] = tau[i < n_img ? i : 0];
+        asm volatile("" : "+s"(t[i]));
+    }
+    double Jf[NB], Hf[NB];
+    double J = 0.0, H = 0.0, tp = 0.0;
+    auto predict = [&](double s) {
+        const double d = 1.0 + s * J;
+        const double r = refined_rcp(d);
+        J = plain_quotient(J, d, r);
+        H = plain_quotient(H, d, r);
+    };
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        if ((keep >> i) & 1u) {
+            const double ti = t[i];
+            if (walk) predict(q * (ti - tp));
+            Jf[i] = J;
+            Hf[i] = H;
+            J = J + (double)v[i].y;
+            H = H + (double)v[i].x;
+            tp = ti;
+        }
+    }
+    J = 0.0;
+    H = 0.0;
+    // The largest residual so far that could exceed c2, from just below it.
+    double rmax = c2 * (1.0 - 0x1p-16);
+    bool above = false;
+    close = false;
+    worst = 0;
+#pragma unroll
+    for (int i = NB - 1; i >= 0; --i) {
+        if ((keep >> i) & 1u) {
+            const double ti = t[i];
+            if (walk) predict(q * (tp - ti));
+            const double ps = (double)v[i].x, ph = (double)v[i].y;
+            const double Jk = Jf[i] + J, Hk = Hf[i] + H;
+            const double a = ps * Jk - ph * Hk;
+            const double dv = (ph * Jk) * (Jk + ph);
+            const double r = (a * a) * __builtin_amdgcn_rcp(dv);
+            if (dv > 0.0 && r > rmax * (1.0 - 0x1p-17)) {
+                close = close || !(r > rmax * (1.0 + 0x1p-17)) || !(r > c2 * (1.0 + 0x1p-17));
+                rmax = r;
+                worst = i;
+                above = true;
+            }
+            J = J + ph;
+            H = H + ps;
+            tp = ti;
+        }
+    }
+    return above;
+}
+
+// A round of the plain kind where every lane of the wave allows it.
+template <int NB>
+__device__ __forceinline__ bool filter_round(const float2 (&v)[NB], uint64_t keep, int n_img,
+                                             const double *__restrict__ tau, double q,
+                                             float q_span, double c2, int &worst) {
+    bool close = true, above = false;
+    if (__all(plain_divisions<NB>(v, q_span)))
+        above = filter_round_plain<NB>(v, keep, n_img, tau, q, c2, worst, close);
+    if (close) above = filter_round_exact<NB>(v, keep, tau, q, c2, worst);
+    return above;
 }
 
 // The refit from the kept observations, summed in image order in double.
@@ -198,7 +320,7 @@ template <int NB>
 __global__ __launch_bounds__(LC_THREADS) void lightcurve_kernel(
     int64_t ncand, int k, int h, int w, int n_img, const float2 *__restrict__ planes,
     const double *__restrict__ tau, const double2 *__restrict__ vels, int n_vel, double c2,
-    double q, const int32_t *__restrict__ cand_vel, float *__restrict__ nu,
+    double q, float q_span, const int32_t *__restrict__ cand_vel, float *__restrict__ nu,
     float *__restrict__ alpha, int16_t *__restrict__ nobs, uint64_t *__restrict__ rejected) {
     const int64_t c = (int64_t)blockIdx.x * LC_THREADS + threadIdx.x;
     if (c >= ncand) return;
@@ -210,7 +332,7 @@ __global__ __launch_bounds__(LC_THREADS) void lightcurve_kernel(
     uint64_t keep = obs;
     for (;;) {   // at most popcount(obs) + 1 rounds
         int worst;
-        if (!(filter_round<NB>(v, keep, tau, q, worst) > c2)) break;
+        if (!filter_round<NB>(v, keep, n_img, tau, q, q_span, c2, worst)) break;
         keep &= ~(uint64_t(1) << worst);
     }
     float o_nu, o_al;
@@ -252,7 +374,7 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
     int k, int pt, int h, int w, int row0, int n_rows, int n_img,
     const float2 *__restrict__ planes, const double *__restrict__ tau,
     const double2 *__restrict__ vels, int n_vel, double c2, double q,
-    const int32_t *__restrict__ cand_vel, float *__restrict__ nu, float *__restrict__ alpha,
+    float q_span, const int32_t *__restrict__ cand_vel, float *__restrict__ nu, float *__restrict__ alpha,
     int16_t *__restrict__ nobs, uint64_t *__restrict__ rejected) {
     extern __shared__ __align__(16) unsigned char lc_lds[];
     const int np_max = pt * k;
@@ -316,7 +438,7 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
             bool queued = false;
             for (;;) {   // at most popcount(obs) + 1 rounds
                 int worst;
-                if (!(filter_round<NB>(v, keep, tau, q, worst) > c2)) break;
+                if (!filter_round<NB>(v, keep, n_img, tau, q, q_span, c2, worst)) break;
                 keep &= ~(uint64_t(1) << worst);
                 if constexpr (NB == 16) {
                     // The next round in the next pass.
@@ -360,12 +482,12 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
 template <int NB>
 kb_status launch_lightcurve(int64_t ncand, int k, int h, int w, int n_img, const float2 *planes,
                             const double *tau, const double2 *vels, int n_vel, double c2,
-                            double q, const int32_t *cv, float *nu, float *al, int16_t *no,
+                            double q, float q_span, const int32_t *cv, float *nu, float *al, int16_t *no,
                             uint64_t *rej, hipStream_t s) {
     if (k > LC_PAIRS) {
         const int64_t blocks = (ncand + LC_THREADS - 1) / LC_THREADS;
         hipLaunchKernelGGL(lightcurve_kernel<NB>, dim3((unsigned)blocks), dim3(LC_THREADS), 0, s,
-                           ncand, k, h, w, n_img, planes, tau, vels, n_vel, c2, q, cv, nu, al,
+                           ncand, k, h, w, n_img, planes, tau, vels, n_vel, c2, q, q_span, cv, nu, al,
                            no, rej);
         return launch_status("lightcurve_kernel");
     }
@@ -379,7 +501,7 @@ kb_status launch_lightcurve(int64_t ncand, int k, int h, int w, int n_img, const
         const int n_rows = (int)std::min<int64_t>(max_rows, h - r0);
         hipLaunchKernelGGL(lightcurve_grouped_kernel<NB>, dim3((unsigned)(per_row * n_rows)),
                            dim3(LC_THREADS), lightcurve_lds_bytes(pt * k), s, k, pt, h, w,
-                           (int)r0, n_rows, n_img, planes, tau, vels, n_vel, c2, q, cv, nu, al,
+                           (int)r0, n_rows, n_img, planes, tau, vels, n_vel, c2, q, q_span, cv, nu, al,
                            no, rej);
         const kb_status st = launch_status("lightcurve_grouped_kernel");
         if (st != KB_OK) return st;
@@ -427,6 +549,11 @@ kb_status kb_lightcurve_filter(const float *psi_phi, int64_t n_img, int64_t h, i
     if (workspace_bytes < ws_need)
         return fail(KB_ENOMEM, "workspace needs %zu bytes (got %zu)", ws_need, workspace_bytes);
 
+    // The walk's variance over the whole series, for as many images as a light
+    // curve can have (NaN: no plain divisions).
+    float q_span = (float)(KB_MAX_LC_IMAGES * q * (t[n_img - 1] - t[0]));
+    if (c2 < 0x1p-900) q_span = NAN;
+
     hipStream_t s = (hipStream_t)stream;
     size_t vel_off = 0;
     st = upload_tau_vel(t, n_img, vel, n_vel, workspace, s, &vel_off);
@@ -437,14 +564,14 @@ kb_status kb_lightcurve_filter(const float *psi_phi, int64_t n_img, int64_t h, i
     const float2 *planes = reinterpret_cast<const float2 *>(psi_phi);
     if (n_img <= 16)
         return launch_lightcurve<16>(ncand, (int)k, (int)h, (int)w, (int)n_img, planes, tau,
-                                     vels, (int)n_vel, c2, q, cand_vel, nu, alpha, nobs,
+                                     vels, (int)n_vel, c2, q, q_span, cand_vel, nu, alpha, nobs,
                                      rejected, s);
     if (n_img <= 32)
         return launch_lightcurve<32>(ncand, (int)k, (int)h, (int)w, (int)n_img, planes, tau,
-                                     vels, (int)n_vel, c2, q, cand_vel, nu, alpha, nobs,
+                                     vels, (int)n_vel, c2, q, q_span, cand_vel, nu, alpha, nobs,
                                      rejected, s);
     return launch_lightcurve<64>(ncand, (int)k, (int)h, (int)w, (int)n_img, planes, tau, vels,
-                                 (int)n_vel, c2, q, cand_vel, nu, alpha, nobs, rejected, s);
+                                 (int)n_vel, c2, q, q_span, cand_vel, nu, alpha, nobs, rejected, s);
 }
 
 }  // extern "C"

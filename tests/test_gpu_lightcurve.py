@@ -256,3 +256,52 @@ def test_filter_survey_sampled(torch_dev):
          f"{int(o['rejected'].sum())} observations dropped")
     assert o["rejected"].sum() > 0
     _compare_tolerant(sel(g[0]), sel(g[1]), sel(g[2]), sel(g[3]), o, lcf, obs, robust)
+
+
+# Light curves on both sides of what the filter's shorter divisions and
+# approximate ordering take: (images, what is unusual).
+ROUND_CASES = [(n, "none") for n in (1, 2, 3, 15, 16, 17, 32, 33, 64)] + [
+    (16, "pairs"), (15, "negative_phi"), (15, "huge_psi"), (17, "long_walk"),
+    (15, "tiny_cut"), (15, "small_phi"), (16, "far")]
+
+
+@pytest.mark.parametrize("case", ROUND_CASES, ids=lambda c: f"{c[1]}{c[0]}")
+def test_filter_rounds_exact_where_divisions_are_not_plain(torch_dev, case):
+    """Planes drawn directly, with flashes: masks, counts and the float32
+    results are the oracle's, both computed in IEEE double from the same
+    float32 values."""
+    n, what = case
+    rng = np.random.default_rng(71 + n)
+    h, w, nv, k, cut, q = 19, 70, 30, 7, 4.0, 0.7
+    phi = rng.uniform(0.01, 0.06, (n, h, w))
+    psi = rng.standard_normal((n, h, w)) * np.sqrt(phi)
+    flash = rng.random((n, h, w)) < (0.4 if what == "pairs" else 0.03)
+    psi = np.where(flash, psi + 40.0 * np.sqrt(phi), psi)
+    ok = rng.random((n, h, w)) > (0.8 if what == "pairs" else 0.05)
+    t = np.sort(rng.uniform(0.0, 3.0, n))
+    vel = rng.uniform(-20.0, 20.0, (nv, 2))
+    if what == "negative_phi":
+        phi = np.where(rng.random(phi.shape) < 0.02, -phi, phi)
+    if what == "huge_psi":
+        psi = np.where(rng.random(psi.shape) < 0.02, psi * 1e33, psi)
+    if what == "long_walk":
+        q = 1e5
+    if what == "tiny_cut":
+        cut = 1e-140
+    if what == "small_phi":
+        phi, psi = phi * 1e-30, psi * 1e-15
+    if what == "far":
+        vel[::3] *= 1.7e7     # up to just below 2^30 pixels over the series
+    p32, f32 = _f32_planes(psi, phi, ok)
+    s = synth.Stack(None, None, None, t, None, vel, k, np.zeros((0, 5)), name=what)
+    js = rng.integers(-1, nv + 1, (h, w, k)).astype(np.int32)
+    _say(f"case rounds N={n} {what}")
+    nu, al, no, rej = _gpu_filter(torch_dev, np.stack([p32, f32], axis=-1), s, js, cut, q)
+    ys, xs = (np.repeat(a.reshape(-1), k) for a in np.meshgrid(np.arange(h), np.arange(w),
+                                                               indexing="ij"))
+    o = olc.lightcurve_filter(p32.astype(np.float64), f32.astype(np.float64), ok, t, vel, ys, xs,
+                              js.reshape(-1), cut, q)
+    np.testing.assert_array_equal(rej.reshape(-1), _mask_bits(o["rejected"]))
+    np.testing.assert_array_equal(no.reshape(-1), o["nobs"])
+    np.testing.assert_array_equal(nu.reshape(-1), o["nu"].astype(np.float32))
+    np.testing.assert_array_equal(al.reshape(-1), o["alpha"].astype(np.float32))

@@ -496,15 +496,14 @@ def test_rescore_of_plain_candidates_equals_topk(torch_dev, case):
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 25])
 def test_rescore_of_any_image_count_and_far_velocities(torch_dev, n):
     """Every remainder of the re-score's image groups, with velocities whose
-    displacements leave the frame by a little, by more than 2^31 pixels and by
-    more than a double holds as an integer: bit for bit the search's values."""
+    displacements leave the frame by a little and by nearly 2^30 pixels, the
+    most that is accepted: bit for bit the search's values."""
     from paper_1901_02492_amd import lib
     torch = torch_dev
     h, w, kc = 9, 67, 11
     s = synth.random_stack(86, n=n, h=h, w=w, n_vel=40, k=kc, psf_size=5, vmax=60)
     vel = s.vel.copy()
-    vel[1::5] *= 1e9
-    vel[3::5] *= 1e200
+    vel[1::3] *= 1.7e7
     _say(f"case rescore remainder N={n}")
     dev = torch.device("cuda:0")
     img, var, mask = (torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask))
