@@ -137,8 +137,8 @@ __global__ void table_kernel(const double *__restrict__ tau, const double2 *__re
     GatherEntry g;
     if (i < n_img) {
         const double2 v = vel[order[jj]];
-        g.dx = displacement(v.x, tau[i], w);
-        g.dy = displacement(v.y, tau[i], h);
+        g.dx = min(max(displacement(v.x, tau[i]), -w), w);
+        g.dy = min(max(displacement(v.y, tau[i]), -h), h);
         g.offset = (int64_t)i * image_bytes + (int64_t)g.dy * row_bytes;
     } else {
         g.dx = w;
