@@ -28,12 +28,9 @@ kb_status upload_tau_vel(const double *t, int64_t n_img, const double *vel, int6
 // Send the gather table (planes of `pix_bytes` bytes per pair; velocities in
 // visiting order unless visiting_order is false) and the visiting order to
 // the workspace (workspace_layout offsets).
-// If dy_range is given it receives the smallest and largest row displacement
-// of the table's real entries.
 kb_status upload_table(const double *t, int64_t n_img, const double *vel, int64_t n_vel,
                        int64_t h, int64_t w, int64_t pix_bytes, void *workspace,
-                       hipStream_t stream, bool visiting_order = true,
-                       int32_t *dy_range = nullptr);
+                       hipStream_t stream, bool visiting_order = true);
 
 // Argument checks of kb_search (and its allocation-free variant).
 kb_status check_search_args(const void *planes, int32_t dtype, const float *lp_scale,
@@ -43,13 +40,11 @@ kb_status check_search_args(const void *planes, int32_t dtype, const float *lp_s
                             const void *cand_nobs);
 // Enqueue the search on checked arguments whose tables are already in
 // `workspace` (workspace_layout offsets; the inverse scales of 16-bit planes
-// are written here): dy_range is the smallest and largest row displacement of
-// the table's real entries.
+// are written here).
 kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_scale,
                            int64_t n_img, int64_t h, int64_t w, int64_t n_vel, int64_t k_cand,
                            float *cand_nu, float *cand_alpha, int32_t *cand_vel,
-                           int16_t *cand_nobs, void *workspace, const int32_t dy_range[2],
-                           hipStream_t s);
+                           int16_t *cand_nobs, void *workspace, hipStream_t s);
 
 // One displacement on the device: floor(v * tau + 0.5) as a separate IEEE
 // double multiply, add and floor (no contraction), which rounds exactly as

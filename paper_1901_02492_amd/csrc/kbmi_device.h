@@ -16,53 +16,30 @@
 #ifndef KBMI_STRIP_TILES
 #define KBMI_STRIP_TILES 4      // start-pixel tiles per strip of the tile order
 #endif
-#ifndef KBMI_QUEUE
-#define KBMI_QUEUE 16           // queued candidates per lane before a merge
-#endif
-#ifndef KBMI_PREFETCH
-#define KBMI_PREFETCH 1         // single-stack search: fetch the next table row early
-#endif
-#ifndef KBMI_PIPELINE
-#define KBMI_PIPELINE 1         // single-stack search: keep two velocities' gathers in flight
+#ifndef KBMI_PATCH_TILES
+#define KBMI_PATCH_TILES 64     // consecutive tiles of the strip order that one XCD takes
 #endif
 #ifndef KBMI_SUPER_W
 #define KBMI_SUPER_W 2          // tiles per XCD strip in the super-strip order (0: off)
 #endif
+#ifndef KBMI_SUPER_ROWS
+#define KBMI_SUPER_ROWS 64      // rows after which the XCDs change strips in that order
+#endif
 #ifndef KBMI_PERSIST_BS
-#define KBMI_PERSIST_BS 2       // float32 planes: tiles per block row in the persistent order (0: off)
-#endif
-#ifndef KBMI_PIPE_MAX_LP
-#define KBMI_PIPE_MAX_LP 56     // 16-bit planes: longest list with two velocities' gathers in flight
-#endif
-#ifndef KBMI_PERSIST_LP
-#define KBMI_PERSIST_LP 0       // 16-bit planes also take the persistent order
+#define KBMI_PERSIST_BS 2       // float32 planes: tiles per block row in the persistent order
 #endif
 #ifndef KBMI_PERSIST_SPIN
 #define KBMI_PERSIST_SPIN 4000  // bound of a wave's wait at a generation boundary
 #endif
-
 #ifndef KBMI_PERSIST_PER_CU
 #define KBMI_PERSIST_PER_CU 8   // persistent grid: at most this many one-wave workgroups per CU
 #endif
-#ifndef KBMI_NET_MAX_F32
-#define KBMI_NET_MAX_F32 64     // longest list merged by the comparator network (float32)
-#endif
-#ifndef KBMI_NET_MAX_LP
-#define KBMI_NET_MAX_LP 64      // 16-bit planes
-#endif
-#ifndef KBMI_LP_SC_MIN_KM
-#define KBMI_LP_SC_MIN_KM 0     // 16-bit planes: lists of at least this length read their scales from LDS
-#endif
-// Float32, one batch of images: how many trailing padding slots may be
-// skipped by uniform branches.  1: the survey's 15 images skip their one
-// padding slot (83.5 -> 80.5 ms).  3 also serves 13 and 14 images (13 x
-// 4096^2 at 32000 velocities: 3549 -> 3254 ms) but the two extra branches
-// cost the 15-image search 80.4 -> 81.3 ms.
-#ifndef KBMI_SKIP_TAIL
-#define KBMI_SKIP_TAIL 1
-#endif
-#ifndef KBMI_INTERIOR
-#define KBMI_INTERIOR 1         // start rows with every displaced row in frame skip the row check
+// Queued candidates per lane before a merge.  Eight waves' queues and lists
+// just fit a CU's LDS; a merge takes 16, so a queue of 22 is fuller when one
+// of its wave's lanes runs full (16 -> 22: 12 x 251 x 301, 400 velocities 0.291 ->
+// 0.281 ms; 25 x 1024 x 2048 f16, 4000 velocities 75.2 -> 74.3 ms).
+#ifndef KBMI_QUEUE
+#define KBMI_QUEUE 22
 #endif
 // List lengths compiled for the search (each slot costs registers and
 // compare-and-swap work on every insertion); a search keeps k_cand
@@ -88,7 +65,6 @@ struct StackView {
     int32_t *cand_vel;
     int16_t *cand_nobs;
     uint32_t *sync;            // per-XCD generation counters of the persistent search
-    int row_lo, row_hi;        // start rows whose displaced rows are all in the frame
 };
 
 // One stack of a batched search, as the batch kernel reads it from device
@@ -140,14 +116,13 @@ constexpr int km_for(int k_cand) {
 template <int FMT, int G>
 kb_status launch_search_group(int km, const StackView &v, hipStream_t s);
 template <int FMT, int G>
-kb_status launch_search_batch_group(int km, const BatchJob *jobs, int n_jobs, int n_img_class,
-                                    int k_cand, int generations, uint32_t *sync, int *grid,
-                                    hipStream_t s);
+kb_status launch_search_batch_group(int km, const BatchJob *jobs, int n_jobs, int k_cand,
+                                    int generations, uint32_t *sync, int *grid, hipStream_t s);
 #define KBMI_DECLARE_GROUP(F, G)                                                          \
     template <>                                                                           \
     kb_status launch_search_group<F, G>(int, const StackView &, hipStream_t);             \
     template <>                                                                           \
-    kb_status launch_search_batch_group<F, G>(int, const BatchJob *, int, int, int, int,    \
+    kb_status launch_search_batch_group<F, G>(int, const BatchJob *, int, int, int,         \
                                               uint32_t *, int *, hipStream_t);
 #define KBMI_DECLARE_FMT(F)                                                                 \
     KBMI_DECLARE_GROUP(F, 0) KBMI_DECLARE_GROUP(F, 1) KBMI_DECLARE_GROUP(F, 2)             \
@@ -165,7 +140,7 @@ kb_status launch_search(int fmt, int km, const StackView &v, hipStream_t s);
 // sync: 8 per-XCD counters (zeroed here).  With jobs == nullptr nothing is
 // launched and *grid receives that class's grid.
 kb_status launch_search_batch(int fmt, int km, const BatchJob *jobs, int n_jobs,
-                              int n_img_class, int k_cand, int generations, uint32_t *sync,
+                              int k_cand, int generations, uint32_t *sync,
                               int *grid, hipStream_t s);
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -330,12 +305,20 @@ __device__ inline float score_alpha(float P, float nu, float F, float r) {
 // enumerated in strips `strip` tiles wide (all rows of a strip, then the next
 // strip) so that consecutive workgroups cover a compact 2-D patch, and the
 // workgroup index is remapped so that each of the 8 XCDs (which receive
-// workgroups round-robin) walks one contiguous range of that order and its
-// L2 sees neighbouring patches.
+// workgroups round-robin) takes KBMI_PATCH_TILES consecutive tiles of that
+// order (one patch, whose gathers share its L2) at a time.  The patches go
+// round the XCDs because a tile's work is the images its trajectories stay in,
+// which changes across the frame: with one contiguous range each, the launch
+// waited for the XCD of the left-most columns (12 x 251 x 301, 400 velocities: 0.314
+// -> 0.300 ms).
 __device__ inline int xcd_remap(int b, int nblocks) {
     const int xcd = b & 7, k = b >> 3;
-    const int q = nblocks >> 3, r = nblocks & 7;
-    return xcd * q + (xcd < r ? xcd : r) + k;
+    constexpr int P = KBMI_PATCH_TILES;
+    const int full = nblocks / (8 * P) * (8 * P);
+    if (b < full) return (k / P * 8 + xcd) * P + k % P;
+    // The rest of the order: one contiguous range each.
+    const int q = (nblocks - full) >> 3, r = (nblocks - full) & 7;
+    return full + xcd * q + (xcd < r ? xcd : r) + (k - (full >> 3));
 }
 
 __device__ inline void strip_tile(int t, int nseg, int h, int strip, int &row, int &seg) {
@@ -355,18 +338,20 @@ __device__ inline void strip_tile(int t, int nseg, int h, int strip, int &row, i
 }
 
 // Super-strip order (used when nseg is a multiple of 8 * sw): the frame is
-// cut into vertical super-strips 8 * sw tiles wide; within one, XCD x owns
-// the sw-tile strip x and walks it top to bottom.  The eight XCDs then sweep
-// down the same super-strip together, so the rows that later start rows
-// gather again (every velocity reaches up to the longest displacement) stay
-// within a window the memory-side cache can hold.
+// cut into vertical super-strips 8 * sw tiles wide; the eight XCDs sweep down
+// one together, each in one of its sw-tile strips, so the rows that later
+// start rows gather again (every velocity reaches up to the longest
+// displacement) stay within a window the memory-side cache can hold.  Every
+// KBMI_SUPER_ROWS rows each XCD moves one strip to the right, so that none
+// keeps the columns whose trajectories see the most images (25 x 1024 x 2048 f16,
+// 4000 velocities: 88.4 -> 76.0 ms).
 __device__ inline void superstrip_tile(int b, int h, int sw, int &row, int &seg) {
     const int xcd = b & 7, m = b >> 3;
     const int per = sw * h;
     const int ss = m / per;
     const int rem = m - ss * per;
     row = rem / sw;
-    seg = (ss * 8 + xcd) * sw + (rem - row * sw);
+    seg = (ss * 8 + ((xcd + row / KBMI_SUPER_ROWS) & 7)) * sw + (rem - row * sw);
 }
 
 struct TileMap {
@@ -385,28 +370,37 @@ struct TileMap {
 // Persistent order: the grid is exactly the number of workgroups the GPU
 // holds at once, and workgroup w processes one tile per generation.  In a
 // generation, XCD x (workgroups w = 8k + x, dispatched round-robin over the
-// XCDs) covers one block of bs x brows tiles (k -> row k / bs, seg k % bs),
-// the eight XCDs take eight side-by-side blocks, and generations move down
-// the frame, then to the next eight block columns.  Waves that start a
-// generation together walk the velocities roughly in step, so one velocity's
-// gathers find the rows the block read for the previous ones still in L2.
-// Every in-frame tile belongs to exactly one (generation, workgroup); slots
-// past the frame's edge are skipped.
+// XCDs) covers one block of bs x brows tiles (k -> row k / bs, seg k % bs).
+// The eight XCDs take eight side-by-side blocks and generations move down the
+// frame, then to the next eight block columns (the last columns, fewer than
+// eight, are taken row by row, eight blocks a generation).  Waves that start
+// a generation together walk the velocities roughly in step, so one
+// velocity's gathers find the rows the block read for the previous ones
+// still in L2.  The XCDs change columns every generation: a block's work
+// falls with the images its trajectories still see, and an XCD that kept the
+// first column had up to 1.5 times the others' (13 x 1024^2, 32000 velocities:
+// 186 -> 167 ms).  Every in-frame tile belongs to exactly one (generation,
+// workgroup); slots past the frame's edge are skipped.
+inline __host__ __device__ int block_generations(int nbc, int nbr) {
+    return (nbc >> 3) * nbr + ((nbc & 7) * nbr + 7) / 8;
+}
 struct PersistMap {
     int nseg, h;
     int bs, brows;     // block: bs tiles wide, brows rows tall (bs * brows = grid / 8)
     int nbc, nbr;      // blocks per row of blocks, rows of blocks
-    int generations;   // ceil(nbc / 8) * nbr
+    int generations;   // block_generations(nbc, nbr)
     int spin;          // bound of a wave's wait at a generation boundary (0: no wait)
     __device__ inline bool map(int gen, int w, int &row, int &seg) const {
         const int xcd = w & 7, k = w >> 3;
-        const int sc = gen / nbr;
-        const int br = gen - sc * nbr;
-        const int bc = sc * 8 + xcd;
+        const int sc = min(gen / nbr, nbc >> 3);
+        const int wide = min(8, nbc - 8 * sc);
+        const int g = gen - sc * nbr;
+        const int id = 8 * g + ((xcd + g) & 7);
+        const int br = id / wide, bc = 8 * sc + id - br * wide;
         const int q = k / bs;
         row = br * brows + q;
         seg = bc * bs + (k - q * bs);
-        return bc < nbc && row < h && seg < nseg;
+        return br < nbr && row < h && seg < nseg;
     }
 };
 
@@ -432,9 +426,31 @@ __device__ inline float lp_value(uint32_t bits16, int fmt) {
 // Trajectory search.
 //
 // One wave (one workgroup) owns 64 adjacent start pixels of one row and walks
-// every velocity in the host-chosen visiting order.  Per velocity each lane
-// gathers its trajectory's N (psi, phi) pairs (one coalesced 512-byte run per
-// image across the wave), sums them in image order and scores nu.
+// every velocity.  Per velocity each lane gathers its trajectory's (psi, phi)
+// pairs (one coalesced 512-byte run per image across the wave), sums them in
+// image order and scores nu.
+//
+// What bounds it.  The vector-memory path returns a wave's 8-byte load in
+// 16.4 cycles and its 4-byte load in 10.7, whether it hits, misses the frame
+// or finds a zero-length buffer; with a load per image that path is busy 93 %
+// of the time (13 x 1024^2, 32000 velocities: 1.336e11 of 1.436e11 cycles), the
+// vector issue 37 %.  So the loads that read nothing are the cost to remove.  A
+// linear trajectory that leaves the frame does not return (displacements
+// grow with the image in both axes), so a tile sees a velocity in a prefix
+// 1 .. m of the images: the velocities are sorted into classes by m, a chunk
+// at a time, and each class is visited by a loop with exactly its number of
+// loads, rounded up to even, so that the wait before a batch's sums counts the
+// loads behind it (a branch around single loads makes the compiler wait for
+// all: 25 images, float32, 902 -> 1655 ms).  m comes from a binary search in
+// the table's own displacements, a velocity per lane.  A load per image ->
+// classes and balanced tile orders: 13 x 1024^2, 32000 velocities, K = 50
+// 237 -> 165 ms (15.0 -> 8.9 loads a velocity); 12 x 251 x 301, 400 velocities 0.374 ->
+// 0.281; 25 x 1024 x 2048 f16, 4000 velocities, K = 50 79.8 -> 73.8; 9 x 613 x 1187 bf16,
+// 260 velocities, K = 52 1.50 -> 1.17; 15 x 4096^2, 600 velocities, K = 50 (12.8 of 14
+// images seen) 79.5 -> 80.0, bound by the same path at 20 cycles a load, most
+// of them from L2.  Images and velocities keep their order within a class; the
+// sums of a velocity run in image order and the selection does not depend on
+// the order of the velocities, so results are bit for bit those of any order.
 //
 // Per-pixel selection keeps a descending list of KM >= k_cand keys in
 // registers.  Inserting into it costs a compare-and-swap per slot, and the wave
@@ -443,493 +459,368 @@ __device__ inline float lp_value(uint32_t bits16, int fmt) {
 // parked in a per-lane LDS queue of PB entries; the queue is merged into the
 // list only when some lane's queue is full (and at the end).  A candidate that
 // fails the threshold can never enter the final list: the threshold only rises.
+// The merge stands once, outside the class loops (in each of them the list
+// would be copied at every loop's edge and spill: 4x slower): a loop leaves
+// when a queue is full, and its gathers in flight are issued again after the
+// merge.
 //
-// The loads of up to NB images are issued together before they are summed in
-// image order; larger stacks are summed in batches of NB images.  The kernel
-// is bounded to two waves per SIMD: memory-level parallelism comes from the
-// waves, each holding one velocity's NB loads in flight.
+// The kernel is bounded to two waves per SIMD (the list takes the registers):
+// memory-level parallelism comes from the waves, each with two batches' gathers
+// in flight.
 // ---------------------------------------------------------------------------
+constexpr int kChunk = 256;           // velocities classified at once
+constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales fit the LDS
+constexpr int kScaleWords = 2 * kMaxScaleImages + 2 * 16;
+// LDS words of visit_velocities: a chunk's list and classes, then the inverse
+// scales of 16-bit planes.
+constexpr int kVisitWords = kChunk + kChunk / 2 + kChunk / 4 + kScaleWords;
+
 // LDS of a search workgroup: the candidate queue (3 words per entry and
-// lane), also used to stage the output (KM words per lane), then the inverse
-// scales of 16-bit planes of up to kSearchScaleWords / 2 images.
-constexpr int kSearchScaleWords = 128;
+// lane), also used to stage the output (KM words per lane), then the words of
+// visit_velocities.
 template <int KM, int PB>
 constexpr int search_queue_words() {
     return (3 * PB > KM ? 3 * PB : KM) * 64;
 }
 template <int KM, int PB>
 constexpr int search_lds_words() {
-    return search_queue_words<KM, PB>() + kSearchScaleWords;
+    return search_queue_words<KM, PB>() + kVisitWords;
 }
 
-// The gathers of one tile (start row `row`, start columns seg*64 .. seg*64+63)
-// for every velocity in the host-chosen visiting order: per velocity each lane
-// sums its trajectory's N (psi, phi) pairs in image order (one coalesced
-// 64 * pair-size run per image across the wave) and counts n_obs, then calls
-// finish(j, Psi, Phi, n_obs) with the velocity's original index j.  All
-// scalar arguments are wave-uniform.
-//   NB        loads per batch (8 or 16; the table stride is a multiple of 16)
-//   PF        fetch the next table row while the gathers are in flight
-//   PIPE      two batches' gathers in flight (PF only; costs a second buffer)
-//   MB        more images than one batch (launched for n_img > NB only)
-//   INTERIOR  every displaced row of this start row is inside the frame
-//   LDS_SC    16-bit planes in one batch: the inverse scales are read from LDS
-//             per velocity instead of held in 2 NB vector registers (for
-//             long lists, whose slots need those registers)
-//   sc_lds    16-bit planes with MB or LDS_SC: LDS for kSearchScaleWords
-//             inverse scales
-template <int NB, int FMT, bool PF, bool PIPE, bool MB, bool INTERIOR, bool LDS_SC,
-          class Finish>
-__device__ __forceinline__ void visit_velocities(
-    float *sc_lds, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
-    int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
-    const int32_t *__restrict__ vel_index, int n_vel, int row, int seg, Finish &&finish) {
-    const int lane = (int)threadIdx.x;
-    const int x0 = seg * 64 + lane;
+// Sums of one pixel along one trajectory.
+template <int FMT>
+struct PixelSums {
+    float P = 0.f, F = 0.f;
+    uint32_t c = 0u;
+    // float32 planes: psi, phi as loaded.
+    __device__ inline void add(u32x2 v) {
+        uint32_t m;
+        P += __uint_as_float(v.x);
+        F += __uint_as_float(v.y);
+        // n_obs: the stored phi is nonzero exactly at valid pixels.
+        // min(bits, 1) as one vector instruction: the compiler's
+        // compare-and-carry form routes each term through a scalar mask and
+        // needs wait states before its use.
+        asm("v_min_u32 %0, %1, 1" : "=v"(m) : "v"(v.y));
+        c += m;
+    }
+    // 16-bit planes: the packed pair and its image's inverse scales, exact
+    // powers of two (the product is exact, so each FMA rounds once).
+    __device__ inline void add(uint32_t v, float isp, float isf) {
+        uint32_t m;
+        P = fmaf(lp_value(v & 0xFFFFu, FMT), isp, P);
+        F = fmaf(lp_value(v >> 16, FMT), isf, F);
+        // Both halves at once: min(psi16, 1) | min(phi16, 1) << 16; at most
+        // 32767 terms, so the low half never carries.
+        asm("v_pk_min_u16 %0, %1, %2" : "=v"(m) : "v"(v), "v"(0x00010001u));
+        c += m;
+    }
+    __device__ inline uint32_t count() const { return FMT == KB_F32 ? c : c >> 16; }
+};
+
+// A tile (64 start pixels of one row, from column seg * 64 on) and what its
+// gathers share.  All members but x and start are wave-uniform.
+template <int FMT>
+struct Tile {
     typedef typename PlaneLoad<FMT>::type LoadT;
-    constexpr uint32_t kPix = FMT == KB_F32 ? 8u : 4u;   // bytes per (psi, phi) pair
-    const uint32_t row_bytes = (uint32_t)w * kPix;
-    const const_i32 *visit = (const const_i32 *)(const void *)vel_index;
-    // Byte address of the start row in image 0; a table entry's offset moves
-    // it to the displaced row of its image.
-    const uint64_t row0 = reinterpret_cast<uint64_t>(planes) + (uint64_t)row * row_bytes;
-    // Fetch entries [i0, i0 + NB) of table row jj (wide scalar loads).
-    auto fetch = [&](int jj, int i0, i32x4(&e)[NB]) {
-        const const_i32x4 *t4 =
-            (const const_i32x4 *)(const void *)(disp + (size_t)jj * disp_stride + i0);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) e[b] = t4[b];
-    };
-    // Issue the gathers of one batch of table entries, from entry `from` on
-    // (a compile-time 0 or 1).  A row outside the frame (padding entries
-    // included) gets a zero-length buffer, so its loads return 0 and add
-    // nothing, with no branch.  With a record count of 0 every lane fails the
-    // range check before an address is formed, so the base of such a buffer
-    // (which may point outside the planes) is never dereferenced.  no_entry0:
-    // entry 0 (image 0, whose pair is loaded once per tile) gets a zero-length
-    // buffer too, so its load touches no memory.
-    // nl: entries of this batch that hold images (later ones are padding).
-    // Float32 planes skip the padding slots' loads (their registers hold 0).
-    // 16-bit planes issue them like the others: a padding entry's column
-    // x0 + w fails the range check (and its row, outside the frame, gets a
-    // zero-length buffer off interior tiles), so the load returns 0 and
-    // touches no memory; with no branch, the wait before a batch's sums counts
-    // exactly the loads of the batch behind it (25 images at 4000 velocities:
-    // 16-bit 974 -> 889 ms; float32 902 -> 1655 ms, so float32 keeps the skip).
-    // skip_last (float32 planes): one batch holding every image but the last
-    // slot (n_img = NB - 1, the survey's 15 images): that slot's load is
-    // skipped by one uniform branch, which leaves the wait before the
-    // previous batch's sums at most one load short: 83.5 -> 80.5 ms on the
-    // survey stack.  16-bit planes issue it (the branch measured 57.8 ->
-    // 61.2 ms there).
-    auto issue = [&](const i32x4(&e)[NB], auto &v, int from, bool no_entry0, int nl,
-                     bool skip_last = false) {
-        constexpr int NV = (int)(sizeof(v) / sizeof(v[0]));   // NB, or NB / 2
-#pragma unroll
-        for (int b = 0; b < NV; ++b) {
-            if (b < from) continue;
-            const bool tail = KBMI_SKIP_TAIL == 1
-                                  ? (b == NV - 1 && skip_last)
-                                  : (skip_last && b >= NV - KBMI_SKIP_TAIL && b >= n_img);
-            if ((FMT == KB_F32 && b >= nl) || tail) {
-                v[b] = LoadT{};
-                continue;
-            }
-            const uint64_t off = ((uint64_t)(uint32_t)e[b].w << 32) | (uint32_t)e[b].z;
-            // Interior tiles: every real entry's row is in the frame; a padding
-            // entry's column (x0 + w) fails the buffer's range check instead.
-            // 16-bit planes over several batches issue up to 15 padding slots
-            // per velocity; there an entry with dy >= h (padding, or a
-            // trajectory that has left the frame, out of it for any start row)
-            // gets a zero-length buffer, because lanes that fail the range check
-            // of a non-empty buffer cost far more than a buffer that holds
-            // nothing (25 images: 1110 -> 882 ms).  Elsewhere the extra scalar
-            // compare costs more than it saves.
-            constexpr bool kPadCheck = MB && FMT != KB_F32;
-            bool in_rows = INTERIOR ? (!kPadCheck || e[b].y < h)
-                                    : (unsigned)(row + e[b].y) < (unsigned)h;
-            if (b == 0) in_rows = in_rows && !no_entry0;
-            const i32x4 rs = buffer_words(row0 + off, in_rows ? row_bytes : 0u);
-            if constexpr (FMT == KB_F32)
-                v[b] = raw_load_b64(rs, (x0 + e[b].x) * (int)kPix, 0, 0);
-            else
-                v[b] = raw_load_b32(rs, (x0 + e[b].x) * (int)kPix, 0, 0);
-        }
-    };
-    // Sum in image order.  Empty slots hold +0, which leaves every sum
-    // unchanged.  16-bit values are decoded and unscaled by an exact power of
-    // two inside the FMA (the product is exact, so the sum rounds once).
-    // 16-bit planes: the inverse scales (1/s_psi, 1/s_phi) of images
-    // [i0, i0 + NB), uniform values.
-    typedef f32x4 Scales[NB / 2];
-    auto load_scales = [&](int i0, Scales &ss) {
-        const const_f32x4 *sc4 = (const const_f32x4 *)(const void *)(inv_scale + i0);
-#pragma unroll
-        for (int q = 0; q < NB / 2; ++q) ss[q] = sc4[q];
-    };
-    // v: a batch of NB loads, or NB / 2 (with as many scale pairs in ss).
-    auto accumulate = [&](const auto &ss, const auto &v, float &P, float &F, int from) {
-        constexpr int NV = (int)(sizeof(v) / sizeof(v[0]));
-        if constexpr (FMT == KB_F32) {
-            (void)ss;
-#pragma unroll
-            for (int b = 0; b < NV; ++b) {
-                if (b < from) continue;
-                P += __uint_as_float(v[b].x);
-                F += __uint_as_float(v[b].y);
-            }
-        } else {
-#pragma unroll
-            for (int b = 0; b < NV; ++b) {
-                if (b < from) continue;
-                const float isp = (b & 1) ? ss[b / 2].z : ss[b / 2].x;
-                const float isf = (b & 1) ? ss[b / 2].w : ss[b / 2].y;
-                P = fmaf(lp_value(v[b] & 0xFFFFu, FMT), isp, P);
-                F = fmaf(lp_value(v[b] >> 16, FMT), isf, F);
-            }
-        }
-    };
-    // n_obs: the stored phi is nonzero exactly at valid pixels; empty slots are 0.
-    auto count = [&](const auto &v, int from) {
-        constexpr int NV = (int)(sizeof(v) / sizeof(v[0]));
-        uint32_t c = 0;
-#pragma unroll
-        for (int b = 0; b < NV; ++b) {
-            if (b < from) continue;
-            if constexpr (FMT == KB_F32) {
-                // min(bits, 1) as one vector instruction: the compiler's
-                // compare-and-carry form routes each term through a scalar
-                // mask and needs wait states before its use.
-                uint32_t m;
-                asm("v_min_u32 %0, %1, 1" : "=v"(m) : "v"(v[b].y));
-                c += m;
-            } else {
-                // Both halves at once: min(psi16, 1) | min(phi16, 1) << 16;
-                // at most 16 terms, so the low half never carries.
-                uint32_t m;
-                asm("v_pk_min_u16 %0, %1, %2" : "=v"(m) : "v"(v[b]), "v"(0x00010001u));
-                c += m;
-            }
-        }
-        if constexpr (FMT != KB_F32) c >>= 16;
-        return c;
-    };
-    // With all images in one batch the scales are loop-invariant: they are
-    // kept in vector registers (the scalar file holds the table row), or in
-    // LDS (LDS_SC).
-    Scales ss0 = {};
-    if constexpr (FMT != KB_F32 && !MB) {
-        if (n_img <= NB) {
-            if constexpr (LDS_SC) {
-                const float *isc = reinterpret_cast<const float *>(inv_scale);
-                for (int q = lane; q < 2 * NB; q += 64) sc_lds[q] = isc[q];
-                __syncthreads();
-            } else {
-                load_scales(0, ss0);
-#pragma unroll
-                for (int q = 0; q < NB / 2; ++q) asm volatile("" : "+v"(ss0[q]));
-            }
+    static constexpr uint32_t kPix = FMT == KB_F32 ? 8u : 4u;   // bytes per (psi, phi) pair
+    uint64_t row0;          // address of the start row in image 0
+    uint32_t row_bytes;
+    const GatherEntry *disp;
+    int stride, n_img, h, row;
+    const const_i32 *visit;
+    uint32_t *list;         // LDS: velocities of the class being visited
+    uint16_t *seen;         // LDS: images a velocity is visible in, image 0 apart
+    uint8_t *cls;           // LDS: its class
+    const float *scale;     // LDS: inverse scales, image i at 2 (i - 1)
+    int x;                  // this lane's start column
+    PixelSums<FMT> start;   // its pixel's sums in image 0
+
+    __device__ inline LoadT load(uint64_t base, uint32_t bytes, int dx) const {
+        const i32x4 rs = buffer_words(base, bytes);
+        if constexpr (FMT == KB_F32) return raw_load_b64(rs, (x + dx) * (int)kPix, 0, 0);
+        else return raw_load_b32(rs, (x + dx) * (int)kPix, 0, 0);
+    }
+};
+
+// The entries of a list from the q-th on, one held by each lane; q stops at
+// the last.
+struct ListCursor {
+    const uint32_t *list;
+    int n, q;
+    uint32_t held;
+    __device__ inline ListCursor(const uint32_t *l, int count, int from)
+        : list(l), n(count), q(from) {
+        load();
+    }
+    __device__ inline void load() { held = list[min((q & ~63) + (int)threadIdx.x, n - 1)]; }
+    __device__ inline uint32_t entry() const {
+        return (uint32_t)__builtin_amdgcn_readlane((int)held, q & 63);
+    }
+    __device__ inline void step() {
+        if (q + 1 < n) {
+            ++q;
+            if ((q & 63) == 0) load();
         }
     }
-    // Inverse scales of batch `part` from LDS.
-    auto lds_scales = [&](int part, Scales &ss) {
-        const f32x4 *s4 = reinterpret_cast<const f32x4 *>(sc_lds + 2 * NB * part);
-#pragma unroll
-        for (int q = 0; q < NB / 2; ++q) ss[q] = s4[q];
+};
+
+// The velocities of the class in t.list from the q-th on, n of them: calls
+// finish(j, P, F, n_obs) for each with the velocity's original index j and the
+// sums of this lane's pixel, until full() (the selection's queue may not hold
+// two more) or the list ends; returns the next q.
+//   NV     loads of a batch.  The last of an odd class is not real: a
+//          zero-length buffer, whose base is never dereferenced
+//   MULTI  a velocity takes several batches (more images than NV)
+// Two batches are in flight: the gathers of the next are issued before the
+// current one is summed and scored, and the table entries of the one after are
+// fetched behind them, into the registers the next one's just left.  Rows of
+// the displaced window are in the frame for every real load, columns are cut by
+// the buffer's range check.  Fetched entries may pass the end of the table by
+// up to 14 (the order array lies there); their loads are not real.
+template <int NV, bool MULTI, int FMT, class Finish, class Full>
+__device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, int n, int q,
+                                           Finish &&finish, Full &&full) {
+    typedef typename Tile<FMT>::LoadT LoadT;
+    q = __builtin_amdgcn_readfirstlane(q);   // (uniform: said again where it is lost)
+    n = __builtin_amdgcn_readfirstlane(n);
+    ListCursor cur(t.list, n, q);
+    // The entries in e: those of velocity `place` of the chunk, part part_f of
+    // parts_f, of which left_f are visible.
+    int part_f = 0, parts_f = 1, left_f = 0, j_f = 0;
+    const const_i32x4 *row_f = nullptr;
+    auto enter = [&]() {
+        const uint32_t ent = cur.entry();
+        const int place = v0 + (int)(ent & 0xFFFFu);
+        left_f = (int)(ent >> 16);
+        part_f = 0;
+        if constexpr (MULTI) parts_f = (left_f + NV - 1) / NV;
+        row_f = (const const_i32x4 *)(const void *)(t.disp + (size_t)place * t.stride + 1);
+        j_f = t.visit[place];
     };
+    auto fetch = [&](i32x4(&e)[NV]) {
+#pragma unroll
+        for (int b = 0; b < NV; ++b) e[b] = row_f[b];
+    };
+    auto advance = [&]() {
+        if (MULTI && ++part_f < parts_f) {
+            row_f += NV;
+            left_f -= NV;
+        } else {
+            cur.step();
+            enter();
+        }
+    };
+    auto issue = [&](const i32x4(&e)[NV], LoadT(&v)[NV]) {
+#pragma unroll
+        for (int b = 0; b < NV; ++b) {
+            const uint64_t off = ((uint64_t)(uint32_t)e[b].w << 32) | (uint32_t)e[b].z;
+            const bool real = (MULTI || b == NV - 1) ? b < left_f : true;
+            v[b] = t.load(t.row0 + off, real ? t.row_bytes : 0u, e[b].x);
+        }
+    };
+    i32x4 e[NV];
+    LoadT va[NV], vb[NV];
+    enter();
+    fetch(e);
+    issue(e, va);
+    int j_c = j_f, parts_c = parts_f;    // of the velocity being summed
+    advance();
+    fetch(e);
+    PixelSums<FMT> sum = t.start;
+    int part = 0;
+    auto step = [&](LoadT(&cur_v)[NV], LoadT(&ahead)[NV]) {
+        issue(e, ahead);
+        const int j_a = j_f, parts_a = parts_f;
+        __builtin_amdgcn_sched_barrier(0);
+        advance();
+        fetch(e);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < NV; ++b) {
+            if constexpr (FMT == KB_F32) {
+                sum.add(cur_v[b]);
+            } else {
+                const float *sc = t.scale + 2 * (NV * part + b);
+                sum.add(cur_v[b], sc[0], sc[1]);
+            }
+        }
+        if (!MULTI || ++part == parts_c) {
+            part = 0;
+            if (q < n) finish(j_c, sum.P, sum.F, sum.count());
+            ++q;
+            sum = t.start;
+        }
+        j_c = j_a;
+        parts_c = parts_a;
+    };
+    // Two batches a turn with one way out (an exit between them would cost the
+    // compiler its scalar registers): at most two velocities end between two
+    // chances to leave.  A velocity left in the middle is started again.
+    do {
+        step(va, vb);
+        step(vb, va);
+    } while (q < n && !full());
+    return min(q, n);
+}
+
+// Every velocity of one tile in the same way without classes: 16-bit planes
+// of more images than the LDS holds scales for.
+template <int FMT, class Finish, class Full>
+__device__ __forceinline__ int visit_serial(const Tile<FMT> &t, const float2 *inv_scale,
+                                            int n_vel, int q, Finish &&finish, Full &&full) {
+    constexpr int NB = 8;
+    typedef typename Tile<FMT>::LoadT LoadT;
+    do {
+        const const_i32x4 *row =
+            (const const_i32x4 *)(const void *)(t.disp + (size_t)q * t.stride);
+        PixelSums<FMT> sum;
+        for (int i0 = 0; i0 < t.n_img; i0 += NB) {   // (the row is padded to 16 entries)
+            LoadT v[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const i32x4 e = row[i0 + b];
+                const uint64_t off = ((uint64_t)(uint32_t)e.w << 32) | (uint32_t)e.z;
+                const bool in = (unsigned)(t.row + e.y) < (unsigned)t.h;
+                v[b] = t.load(t.row0 + off, in ? t.row_bytes : 0u, e.x);
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if constexpr (FMT == KB_F32) sum.add(v[b]);
+                else sum.add(v[b], inv_scale[i0 + b].x, inv_scale[i0 + b].y);
+            }
+        }
+        finish(t.visit[q++], sum.P, sum.F, sum.count());
+    } while (q < n_vel && !full());
+    return q;
+}
+
+#define KB_BATCH_LIST(X) X(2) X(4) X(6) X(8) X(10) X(12) X(14) X(16)
+
+// Every velocity of one tile (start row `row`, start columns seg*64 ..
+// seg*64+63): calls finish(j, P, F, n_obs) with the velocity's original index
+// j and the sums of this lane's pixel, and drain() where full().  All scalar
+// arguments are wave-uniform.  words: kVisitWords of LDS; MAXNV: loads of a
+// batch, at most.
+template <int FMT, int MAXNV, class Finish, class Full, class Drain>
+__device__ __forceinline__ void visit_velocities(
+    uint32_t *words, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
+    int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
+    const int32_t *__restrict__ vel_index, int n_vel, int row, int seg, Finish &&finish,
+    Full &&full, Drain &&drain) {
+    const int lane = (int)threadIdx.x;
+    Tile<FMT> t;
+    t.row_bytes = (uint32_t)w * Tile<FMT>::kPix;
+    t.row0 = reinterpret_cast<uint64_t>(planes) + (uint64_t)row * t.row_bytes;
+    t.disp = disp;
+    t.stride = disp_stride;
+    t.n_img = n_img;
+    t.h = h;
+    t.row = row;
+    const int x_first = seg * 64, x_last = min(seg * 64 + 63, w - 1);
+    t.visit = (const const_i32 *)(const void *)vel_index;
+    t.list = words;
+    t.seen = reinterpret_cast<uint16_t *>(words + kChunk);
+    t.cls = reinterpret_cast<uint8_t *>(words + kChunk + kChunk / 2);
+    float *scale = reinterpret_cast<float *>(words + kChunk + kChunk / 2 + kChunk / 4);
+    t.scale = scale;
+    t.x = x_first + lane;
+    if (FMT != KB_F32 && n_img > kMaxScaleImages) {
+        for (int q = 0; q < n_vel;) {
+            q = visit_serial<FMT>(t, inv_scale, n_vel, q, finish, full);
+            if (full()) drain();
+        }
+        return;
+    }
+    if constexpr (FMT != KB_F32) {
+        // Image 1 first (0 past the last image: a gather there reads 0).
+        const float *isc = reinterpret_cast<const float *>(inv_scale + 1);
+        for (int q = lane; q < kScaleWords; q += 64) scale[q] = q < 2 * n_img - 2 ? isc[q] : 0.f;
+        __syncthreads();
+    }
     // Image 0 is the start image: its displacement is (0, 0) for every
-    // velocity (tau_0 = 0), so the pipelined paths load its pair once per tile
-    // and start every trajectory's sums from it, 0 + value first, exactly the
-    // additions the per-velocity loads would make.
-    float P0 = 0.f, F0 = 0.f;
-    uint32_t c0 = 0;
-    auto hoist_image0 = [&](float isp0, float isf0) {
-        const i32x4 rs = buffer_words(row0, row_bytes);
-        if constexpr (FMT == KB_F32) {
-            const u32x2 v0 = raw_load_b64(rs, x0 * (int)kPix, 0, 0);
-            P0 = 0.f + __uint_as_float(v0.x);
-            F0 = 0.f + __uint_as_float(v0.y);
-            asm("v_min_u32 %0, %1, 1" : "=v"(c0) : "v"(v0.y));
-        } else {
-            const uint32_t v0 = raw_load_b32(rs, x0 * (int)kPix, 0, 0);
-            P0 = fmaf(lp_value(v0 & 0xFFFFu, FMT), isp0, 0.f);
-            F0 = fmaf(lp_value(v0 >> 16, FMT), isf0, 0.f);
-            c0 = (v0 >> 16) != 0u ? 1u : 0u;
-        }
-    };
-    constexpr bool kPipe = PF && PIPE;
-    const bool skip_last = FMT == KB_F32 && !MB &&
-                           (KBMI_SKIP_TAIL == 1 ? n_img == NB - 1 : n_img >= NB - KBMI_SKIP_TAIL);
-    // 16-bit planes of more than one batch keep every image's scales in LDS
-    // (read per batch), up to kMaxLdsScaleImages images.
-    constexpr int kMaxLdsScaleImages = kSearchScaleWords / 2;
-    // The whole visit of one batch after another, for more images than the
-    // pipelined paths take (and lists too long for two batches in flight).
-    auto serial_path = [&]() {
-        for (int jj = 0; jj < n_vel; ++jj) {
-            const int j = visit[jj];
-            float P = 0.f, F = 0.f;
-            uint32_t c = 0;
-            for (int i0 = 0; i0 < n_img; i0 += NB) {
-                i32x4 e[NB];
-                fetch(jj, i0, e);
-                LoadT v[NB];
-                issue(e, v, 0, false, NB);
-                Scales ss = {};
-                if constexpr (FMT != KB_F32) load_scales(i0, ss);
-                accumulate(ss, v, P, F, 0);
-                c += count(v, 0);
+    // velocity (tau_0 = 0), so its pair is loaded once per tile and every
+    // trajectory's sums start from it, 0 + value first.
+    {
+        const auto v0 = t.load(t.row0, t.row_bytes, 0);
+        if constexpr (FMT == KB_F32) t.start.add(v0);
+        else t.start.add(v0, inv_scale[0].x, inv_scale[0].y);
+    }
+    const int ni = n_img - 1;
+    constexpr int kMulti = MAXNV / 2;    // classes: 0, NV / 2, kMulti + NV / 2 of several parts
+    for (int v0 = 0; v0 < n_vel; v0 += kChunk) {
+        const int nc = min(kChunk, n_vel - v0);
+        uint32_t present = 0;   // classes of the chunk's velocities
+        for (int k0 = 0; k0 < nc; k0 += 64) {
+            const int k = k0 + lane;
+            const GatherEntry *entries = disp + (size_t)(v0 + min(k, nc - 1)) * disp_stride;
+            auto visible = [&](int i) {
+                const int dx = entries[i].dx, dy = entries[i].dy;
+                return (unsigned)(row + dy) < (unsigned)h && x_last + dx >= 0 &&
+                       x_first + dx < w;
+            };
+            int m = ni, out = ni;
+            if (ni > 0 && !visible(ni)) m = 0;
+            while (__any(out - m > 1)) {
+                const int i = (m + out) >> 1;
+                const bool see = visible(i);
+                if (out - m > 1) (see ? m : out) = i;
             }
-            finish(j, P, F, c);
+            const int parts = (m + MAXNV - 1) / MAXNV;
+            const int nv = parts <= 1 ? (m + 1) / 2 : ((m + parts - 1) / parts + 1) / 2;
+            const int c = nv + (parts > 1 ? kMulti : 0);
+            t.seen[k] = (uint16_t)m;
+            t.cls[k] = (uint8_t)c;
+            uint64_t todo = __ballot(k < nc);
+            while (todo != 0) {
+                const int c0 = __builtin_amdgcn_readlane(c, __builtin_ctzll(todo));
+                present |= 1u << c0;
+                todo &= ~__ballot(c == c0);
+            }
         }
-    };
-    // NB + 1 <= n_img <= NB + NB / 2 + 1 (17 to 25 images): image 0 hoisted,
-    // the other images fill one batch of NB (images 1..NB) and one of NB / 2
-    // (images NB + 1 .. NB + NB / 2), with two batches in flight: at most
-    // NB / 2 padding slots per velocity, none at 25 images, where the
-    // general sequence below issues 2 NB - 1 slots for 24 images.  The 16-bit
-    // search is bound by issued load instructions (padding slots cost as much
-    // as real ones).  Same sums in the same image order.  16-bit planes only:
-    // float32 planes skip their padding slots' loads already, and the second
-    // path spills the float32 kernels' registers.
-    auto split_path = [&]() {
-        constexpr int NH = NB / 2;
-        if constexpr (FMT != KB_F32) {
-            // Inverse scales of images 1 .. NB + NH into LDS, image 1 first, so
-            // that each batch reads whole f32x4 words (the table of scales
-            // holds 2 * table_stride(n_img) >= 2 (NB + NH + 1) floats).
-            const float *isc = reinterpret_cast<const float *>(inv_scale);
-            for (int q = lane; q < 2 * (NB + NH); q += 64) sc_lds[q] = isc[q + 2];
+        while (present != 0) {
+            const int c0 = __builtin_ctz(present);
+            present &= present - 1;
+            int n = 0;
+            for (int k0 = 0; k0 < nc; k0 += 64) {
+                const int k = k0 + lane;
+                const bool hit = k < nc && t.cls[k] == c0;
+                const uint64_t b = __ballot(hit);
+                if (hit)
+                    t.list[n + __builtin_amdgcn_mbcnt_hi(
+                                   (uint32_t)(b >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0))] =
+                        (uint32_t)k | ((uint32_t)t.seen[k] << 16);
+                n += __builtin_popcountll(b);
+            }
             __syncthreads();
-            hoist_image0(isc[0], isc[1]);
-        } else {
-            hoist_image0(1.f, 1.f);
-        }
-        const int nl_b = n_img - 1 - NB;          // images in batch B (0 .. NH)
-        const int last = n_vel - 1;
-        auto fetch_b = [&](int jj, i32x4(&e)[NB]) {
-            const const_i32x4 *t4 = (const const_i32x4 *)(const void *)(
-                disp + (size_t)jj * disp_stride + 1 + NB);
-#pragma unroll
-            for (int b = 0; b < NH; ++b) e[b] = t4[b];
-        };
-        i32x4 e[NB];
-        LoadT va[NB], vb[NH];
-        fetch(0, 1, e);
-        issue(e, va, 0, false, NB);               // A(0): images 1 .. NB
-        fetch_b(0, e);
-        int jn = last < 1 ? last : 1;
-        for (int jj = 0; jj < n_vel; ++jj) {
-            const int j = visit[jj];
-            issue(e, vb, 0, false, nl_b);         // B(jj) behind A(jj)
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(jn, 1, e);
-            __builtin_amdgcn_sched_barrier(0);
-            float P = P0, F = F0;
-            uint32_t c = c0;
-            {
-                Scales ss = {};
-                if constexpr (FMT != KB_F32) lds_scales(0, ss);
-                accumulate(ss, va, P, F, 0);
-                c += count(va, 0);
-            }
-            issue(e, va, 0, false, NB);           // A(jj + 1) (the last repeats)
-            __builtin_amdgcn_sched_barrier(0);
-            fetch_b(jn, e);
-            __builtin_amdgcn_sched_barrier(0);
-            {
-                f32x4 ssb[NH / 2] = {};
-                if constexpr (FMT != KB_F32) {
-                    const f32x4 *s4 = reinterpret_cast<const f32x4 *>(sc_lds + 2 * NB);
-#pragma unroll
-                    for (int q = 0; q < NH / 2; ++q) ssb[q] = s4[q];
+            for (int q = 0; q < n;) {
+                if (c0 == 0) {
+                    do {
+                        const int k =
+                            __builtin_amdgcn_readfirstlane((int)(t.list[q++] & 0xFFFFu));
+                        finish(t.visit[v0 + k], t.start.P, t.start.F, t.start.count());
+                    } while (q < n && !full());
                 }
-                accumulate(ssb, vb, P, F, 0);
-                c += count(vb, 0);
+#define KB_CASE(NV)                                                                      \
+    if constexpr (NV <= MAXNV) {                                                         \
+        if (c0 == NV / 2) q = visit_class<NV, false, FMT>(t, v0, n, q, finish, full);    \
+    }                                                                                    \
+    if constexpr (NV <= MAXNV && NV > MAXNV / 2) {                                       \
+        if (c0 == kMulti + NV / 2) q = visit_class<NV, true, FMT>(t, v0, n, q, finish, full); \
+    }
+                KB_BATCH_LIST(KB_CASE)
+#undef KB_CASE
+                if (full()) drain();
             }
-            finish(j, P, F, c);
-            jn = jj + 2 < last ? jj + 2 : last;
+            __syncthreads();
         }
-    };
-    if constexpr (MB) {
-        // More images than one batch (MB): launched for n_img > NB only.
-        if (FMT != KB_F32 && kPipe && NB == 16 && n_img <= NB + NB / 2 + 1) {
-            if constexpr (FMT != KB_F32) split_path();
-        } else if (kPipe && (FMT == KB_F32 || n_img <= kMaxLdsScaleImages)) {
-            // Each velocity's table row is read as nbat batches of NB entries,
-            // and the batches of all velocities form one sequence with two
-            // batches in flight (the gathers of batch q+1 are issued before
-            // batch q is summed, the entries of q+2 fetched behind them).  A
-            // velocity's sums run over its batches in image order and it is
-            // scored after its last batch.  Batch 0 of each velocity skips
-            // image 0's memory access (hoisted, as above).
-            const int nbat = (n_img + NB - 1) / NB;
-            if constexpr (FMT != KB_F32) {
-                // (1/s_psi, 1/s_phi) of every image (padding 0) into LDS.
-                const float *isc = reinterpret_cast<const float *>(inv_scale);
-                for (int q = lane; q < 2 * nbat * NB; q += 64) sc_lds[q] = isc[q];
-                __syncthreads();
-                hoist_image0(sc_lds[0], sc_lds[1]);
-            } else {
-                hoist_image0(1.f, 1.f);
-            }
-            const int nq = n_vel * nbat;
-            const int lastq = nq - 1;
-            // Positions (velocity, part) of the batch being summed and of the
-            // batch whose entries sit in e; they advance one batch per step (the
-            // latter stops at the last batch, which the end then repeats).
-            int jj_c = 0, p_c = 0;       // (jj_c is kept for symmetry with the fetch side)
-            int jj_f = 0, p_f = 0;
-            auto advance = [&](int &jj_, int &p_) {
-                if (++p_ == nbat) {
-                    p_ = 0;
-                    ++jj_;
-                }
-            };
-            // Image entries of the last batch of a velocity (the rest pad).
-            const int nl_last = n_img - (nbat - 1) * NB;
-            i32x4 e[NB];
-            LoadT va[NB], vb[NB];
-            fetch(jj_f, p_f * NB, e);
-            issue(e, va, 0, true, NB);
-            int jc = visit[0];           // velocity index of the batch being summed
-            int q_f = 1;                 // flat index of the batch whose entries are in e
-            advance(jj_f, p_f);
-            fetch(jj_f, p_f * NB, e);
-            int je = visit[jj_f];
-            float P = P0, F = F0;
-            uint32_t c = c0;
-            auto step = [&](LoadT(&cur)[NB], LoadT(&ahead)[NB]) {
-                // batch q + 1 (repeats the last at the end)
-                issue(e, ahead, 0, p_f == 0, p_f == nbat - 1 ? nl_last : NB);
-                const int ja = je;
-                __builtin_amdgcn_sched_barrier(0);
-                if (q_f < lastq) {
-                    ++q_f;
-                    advance(jj_f, p_f);
-                }
-                fetch(jj_f, p_f * NB, e);
-                je = visit[jj_f];
-                __builtin_amdgcn_sched_barrier(0);
-                Scales ss = {};
-                if constexpr (FMT != KB_F32) lds_scales(p_c, ss);
-                accumulate(ss, cur, P, F, 0);
-                c += count(cur, 0);
-                if (p_c == nbat - 1) {
-                    finish(jc, P, F, c);
-                    P = P0;
-                    F = F0;
-                    c = c0;
-                }
-                advance(jj_c, p_c);
-                jc = ja;
-            };
-            int q = 0;
-            for (; q + 1 < nq; q += 2) {
-                step(va, vb);
-                step(vb, va);
-            }
-            if (q < nq) step(va, vb);
-        } else {
-            serial_path();
-        }
-    } else if (n_img <= NB && kPipe) {
-        // Two velocities in flight: the gathers of visit jj+1 are issued
-        // before visit jj is summed and scored, and the table row of jj+2 is
-        // fetched behind them (into the registers the row of jj+1 just left).
-        // The load buffers alternate, so the loop runs in pairs of visits; a
-        // visit past the end repeats the last row and is never scored.
-        if constexpr (LDS_SC) hoist_image0(sc_lds[0], sc_lds[1]);
-        else hoist_image0(ss0[0].x, ss0[0].y);
-        i32x4 e[NB];
-        LoadT va[NB], vb[NB];
-        fetch(0, 0, e);
-        issue(e, va, 1, false, NB, skip_last);
-        const int last = n_vel - 1;
-        int j_cur = visit[0];
-        int nxt = last < 1 ? last : 1;
-        fetch(nxt, 0, e);
-        int j_nxt = visit[nxt];
-        auto step = [&](int jj, LoadT(&cur)[NB], LoadT(&ahead)[NB]) {
-            issue(e, ahead, 1, false, NB, skip_last);  // visit jj + 1
-            __builtin_amdgcn_sched_barrier(0);
-            const int n2 = jj + 2 < last ? jj + 2 : last;
-            fetch(n2, 0, e);
-            const int j2 = visit[n2];
-            __builtin_amdgcn_sched_barrier(0);
-            float P = P0, F = F0;
-            if constexpr (LDS_SC) {
-                Scales ss = {};
-                lds_scales(0, ss);
-                accumulate(ss, cur, P, F, 1);
-            } else {
-                accumulate(ss0, cur, P, F, 1);
-            }
-            finish(j_cur, P, F, c0 + count(cur, 1));
-            j_cur = j_nxt;
-            j_nxt = j2;
-        };
-        int jj = 0;
-        for (; jj + 1 < n_vel; jj += 2) {
-            step(jj, va, vb);
-            step(jj + 1, vb, va);
-        }
-        if (jj < n_vel) step(jj, va, vb);
-    } else if (n_img <= NB && PF) {
-        // The next velocity's table row is fetched while this velocity's
-        // gathers are in flight (image 0 hoisted as above).
-        if constexpr (LDS_SC) hoist_image0(sc_lds[0], sc_lds[1]);
-        else hoist_image0(ss0[0].x, ss0[0].y);
-        i32x4 e[NB];
-        fetch(0, 0, e);
-        int j_next = visit[0];
-        for (int jj = 0; jj < n_vel; ++jj) {
-            const int j = j_next;
-            LoadT v[NB];
-            issue(e, v, 1, false, NB, skip_last);
-            // Keep the next row's fetch right behind the gathers (the scheduler
-            // would otherwise sink it below the sums).
-            __builtin_amdgcn_sched_barrier(0);
-            const int jn = jj + 1 < n_vel ? jj + 1 : jj;
-            fetch(jn, 0, e);
-            j_next = visit[jn];
-            __builtin_amdgcn_sched_barrier(0);
-            float P = P0, F = F0;
-            if constexpr (LDS_SC) {
-                Scales ss = {};
-                lds_scales(0, ss);
-                accumulate(ss, v, P, F, 1);
-            } else {
-                accumulate(ss0, v, P, F, 1);
-            }
-            finish(j, P, F, c0 + count(v, 1));
-        }
-    } else if (n_img <= NB) {
-        for (int jj = 0; jj < n_vel; ++jj) {
-            const int j = visit[jj];
-            i32x4 e[NB];
-            fetch(jj, 0, e);
-            LoadT v[NB];
-            issue(e, v, 0, false, NB);
-            float P = 0.f, F = 0.f;
-            if constexpr (LDS_SC) {
-                Scales ss = {};
-                lds_scales(0, ss);
-                accumulate(ss, v, P, F, 0);
-            } else {
-                accumulate(ss0, v, P, F, 0);
-            }
-            finish(j, P, F, count(v, 0));
-        }
-    } else {
-        serial_path();
     }
 }
 
 // The search of one tile (start row `row`, start columns seg*64 .. seg*64+63).
-// All scalar arguments are wave-uniform.  INTERIOR: every displaced row of
-// this start row is inside the frame, so the gathers skip the row check.
-template <int KM, int NB, int PB, int FMT, bool PF, bool MB, bool INTERIOR = false>
+// All scalar arguments are wave-uniform.
+template <int KM, int PB, int FMT>
 __device__ __forceinline__ void search_tile(
     uint32_t *lds, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
@@ -944,11 +835,9 @@ __device__ __forceinline__ void search_tile(
 
     // The list (slots 0..KM-1, descending); with the network merge, slots
     // KM..KM+15 receive the queued batch during a merge.
-    // Longer lists merge one queued entry at a time where the 16 batch slots
-    // would not fit beside the list (16-bit planes also hold their scales).
-    constexpr bool kNet = KM >= 16 && PB == 16 &&
-                          KM <= (FMT == KB_F32 ? KBMI_NET_MAX_F32 : KBMI_NET_MAX_LP);
-    constexpr int KR = kNet ? KM + 16 : KM;
+    constexpr int kBatch = 16;   // queued candidates a network merge takes
+    constexpr bool kNet = KM >= 16 && PB >= kBatch;
+    constexpr int KR = kNet ? KM + kBatch : KM;
     uint64_t key[KR];
     float al[KR];
 #pragma unroll
@@ -975,15 +864,23 @@ __device__ __forceinline__ void search_tile(
     auto merge_queue = [&]() {
         if constexpr (kNet) {
             // The lane's queue (entries past nq read as empty) into the batch
-            // slots, then one network merge.
+            // slots, then one network merge.  What a lane has queued beyond a
+            // batch moves to the front.
 #pragma unroll
-            for (int b = 0; b < PB; ++b) {
+            for (int b = 0; b < kBatch; ++b) {
                 const uint64_t nk = ((uint64_t)q_hi[b * 64 + lane] << 32) | q_lo[b * 64 + lane];
                 const float na = q_al[b * 64 + lane];
                 key[KM + b] = b < nq ? nk : 0;
                 al[KM + b] = b < nq ? na : 0.f;
             }
             net_merge<KM>(key, al);
+#pragma unroll
+            for (int b = kBatch; b < PB; ++b) {
+                q_hi[(b - kBatch) * 64 + lane] = q_hi[b * 64 + lane];
+                q_lo[(b - kBatch) * 64 + lane] = q_lo[b * 64 + lane];
+                q_al[(b - kBatch) * 64 + lane] = q_al[b * 64 + lane];
+            }
+            nq = nq > kBatch ? nq - kBatch : 0;
         } else {
             for (int b = 0; b < PB; ++b) {
                 if (!__any(b < nq)) break;
@@ -993,8 +890,8 @@ __device__ __forceinline__ void search_tile(
                     if (nk > key[KM - 1]) insert(nk, q_al[b * 64 + lane]);
                 }
             }
+            nq = 0;
         }
-        nq = 0;
         thr = key[KM - 1];
     };
     // Score one trajectory (Sec. 2.1.5: nu = Psi / sqrt(Phi), alpha = Psi / Phi)
@@ -1010,19 +907,20 @@ __device__ __forceinline__ void search_tile(
             q_al[nq * 64 + lane] = score_alpha(P, nu, F, r);
             ++nq;
         }
-        if (__any(nq == PB)) merge_queue();
     };
+    // At most two velocities end before it is asked again.
+    auto full = [&]() { return __any(nq >= PB - 1) != 0; };
 
-    // Two velocities' gathers fit beside the list up to KM = 50 with float32
-    // loads and up to KM = 56 with 16-bit loads, whose scales then sit in LDS
-    // (longer lists spill registers with the second load buffer).
-    visit_velocities<NB, FMT, PF,
-                     (KBMI_PIPELINE != 0 && KM <= (FMT == KB_F32 ? 50 : KBMI_PIPE_MAX_LP)), MB,
-                     INTERIOR,
-                     (FMT != KB_F32 && KM >= KBMI_LP_SC_MIN_KM)>(
-        reinterpret_cast<float *>(lds + search_queue_words<KM, PB>()), planes, inv_scale, n_img,
-        h, w, disp, disp_stride, vel_index, n_vel, row, seg, finish);
-    merge_queue();
+    // Loads of a batch: two batches lie beside the list.  16-bit planes, 25
+    // images, K = 50: 16 / 12 / 8 loads 73.8 / 77.0 / 87.9 ms; K = 52 spills with
+    // 16: 1.283 ms against 1.174 with 12 (9 x 613 x 1187); K = 60 and 64 spill
+    // with fewer too: 16 / 12 loads 4.74 / 4.90 and 5.16 / 5.23 ms (15 x 1024^2).
+    constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 12 : 16;
+    visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
+                                  w, disp, disp_stride, vel_index, n_vel, row, seg, finish, full,
+                                  merge_queue);
+    do merge_queue();
+    while (__any(nq > 0));
 
     // Write the rank-ordered list: stage each field through LDS so that the
     // wave's stores cover the contiguous [pixels][k_cand] run of its pixels
@@ -1056,35 +954,29 @@ __device__ __forceinline__ void search_tile(
     }
 }
 
-template <int KM, int NB, int PB, int FMT, bool MB>
+template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, 2) void search_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, int k_cand, TileMap tiles, float *__restrict__ cand_nu,
     float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
-    int16_t *__restrict__ cand_nobs, int row_lo, int row_hi) {
-    __shared__ uint32_t lds[search_lds_words<KM, PB>()];
+    int16_t *__restrict__ cand_nobs) {
+    __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
-    if (KBMI_INTERIOR && row >= row_lo && row < row_hi)
-        search_tile<KM, NB, PB, FMT, KBMI_PREFETCH != 0, MB, true>(
-            lds, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index, n_vel, k_cand,
-            row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
-    else
-        search_tile<KM, NB, PB, FMT, KBMI_PREFETCH != 0, MB>(
-            lds, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index, n_vel, k_cand,
-            row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
+    search_tile<KM, PB, FMT>(lds, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index,
+                             n_vel, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
 
 // The single-stack search in the persistent order (large frames).
-template <int KM, int NB, int PB, int FMT, bool MB>
+template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, 2) void search_persistent_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, PersistMap pm,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
-    int16_t *__restrict__ cand_nobs, uint32_t *sync, int row_lo, int row_hi) {
-    __shared__ uint32_t lds[search_lds_words<KM, PB>()];
+    int16_t *__restrict__ cand_nobs, uint32_t *sync) {
+    __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     uint32_t *xcd_count = sync + (blockIdx.x & 7);
     const uint32_t per_xcd = gridDim.x >> 3;
     int spin = pm.spin;   // 0 once a wait has timed out (the XCD's workgroups are
@@ -1092,14 +984,9 @@ __global__ __launch_bounds__(64, 2) void search_persistent_kernel(
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
         if (pm.map(gen, (int)blockIdx.x, row, seg)) {
-            if (KBMI_INTERIOR && row >= row_lo && row < row_hi)
-                search_tile<KM, NB, PB, FMT, KBMI_PREFETCH != 0, MB, true>(
-                    lds, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index, n_vel,
-                    k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
-            else
-                search_tile<KM, NB, PB, FMT, KBMI_PREFETCH != 0, MB>(
-                    lds, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index, n_vel,
-                    k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
+            search_tile<KM, PB, FMT>(lds, planes, inv_scale, n_img, h, w, disp, disp_stride,
+                                     vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
+                                     cand_vel, cand_nobs);
         }
         // Generation boundary: wait (a bounded time) until every workgroup of
         // this XCD has finished the generation, so its waves start the next
@@ -1130,12 +1017,12 @@ __global__ void zero_words_kernel(uint32_t *p, int n) {
 // persistent search.  Each tile runs exactly the single-stack search, so a
 // stack's results do not depend on what it is batched with.
 // ---------------------------------------------------------------------------
-template <int KM, int NB, int PB, int FMT, bool MB>
+template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__restrict__ jobs_,
                                                              int n_jobs, int generations,
                                                              int spin, int k_cand,
                                                              uint32_t *sync) {
-    __shared__ uint32_t lds[search_lds_words<KM, PB>()];
+    __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     // The descriptors do not change during the launch: read through the
     // constant address space, their fields stay in scalar registers.
     typedef __attribute__((address_space(4))) const BatchJob CJob;
@@ -1163,10 +1050,10 @@ __global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__r
             pm.nbc = jb.nbc;
             pm.nbr = jb.nbr;
             const int gl = li / grid;
-            ok = gl < ((jb.nbc + 7) / 8) * jb.nbr && pm.map(gl, li - gl * grid, row, seg);
+            ok = gl < block_generations(jb.nbc, jb.nbr) && pm.map(gl, li - gl * grid, row, seg);
         }
         if (ok)
-            search_tile<KM, NB, PB, FMT, KBMI_PREFETCH != 0, MB>(
+            search_tile<KM, PB, FMT>(
                 lds, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp, jb.disp_stride,
                 jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
                 jb.cand_vel, jb.cand_nobs);

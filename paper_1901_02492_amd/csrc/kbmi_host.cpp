@@ -79,19 +79,6 @@ void displacement_table(const double *t, int64_t n_img, const double *vel, int64
     }
 }
 
-void dy_extent(const double *t, int64_t n_img, const double *vel, int64_t n_vel,
-               int64_t clamp_h, int32_t out[2]) {
-    int32_t lo = 0, hi = 0;
-    for (int64_t j = 0; j < n_vel; ++j)
-        for (int64_t i = 0; i < n_img; ++i) {
-            const int32_t d = offset_of(vel[2 * j + 1], t[i] - t[0], clamp_h);
-            lo = std::min(lo, d);
-            hi = std::max(hi, d);
-        }
-    out[0] = lo;
-    out[1] = hi;
-}
-
 #ifndef KBMI_HILBERT_ORDER
 #define KBMI_HILBERT_ORDER 1
 #endif

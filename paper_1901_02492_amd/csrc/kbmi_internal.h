@@ -31,11 +31,6 @@ void displacement_table(const double *t, int64_t n_img, const double *vel, int64
 // order gives the same result (ranking uses the original index).
 void velocity_order(const double *vel, int64_t n_vel, int32_t *order);
 
-// Smallest and largest row offset floor(vy * tau_i + 0.5) (clamped to
-// [-clamp_h, clamp_h]) over every velocity and image, with image 0's 0 included.
-void dy_extent(const double *t, int64_t n_img, const double *vel, int64_t n_vel,
-               int64_t clamp_h, int32_t out[2]);
-
 #if defined(__HIPCC__)
 #define KBMI_HD __host__ __device__
 #else

@@ -551,8 +551,7 @@ kb_status check_search_args(const void *planes, int32_t dtype, const float *lp_s
 kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_scale,
                            int64_t n_img, int64_t h, int64_t w, int64_t n_vel, int64_t k_cand,
                            float *cand_nu, float *cand_alpha, int32_t *cand_vel,
-                           int16_t *cand_nobs, void *workspace, const int32_t dy_range[2],
-                           hipStream_t s) {
+                           int16_t *cand_nobs, void *workspace, hipStream_t s) {
     char *wsb = static_cast<char *>(workspace);
     const WorkspaceLayout lay = workspace_layout(n_img, h, w, n_vel);
     StackView sv;
@@ -571,10 +570,6 @@ kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_sc
     sv.cand_vel = cand_vel;
     sv.cand_nobs = cand_nobs;
     sv.sync = reinterpret_cast<uint32_t *>(wsb + lay.sync);
-    // Start rows whose displaced rows are inside the frame for every image and
-    // velocity: their gathers need no row check.
-    sv.row_lo = (int)std::min<int64_t>(h, -(int64_t)dy_range[0]);
-    sv.row_hi = (int)std::max<int64_t>(0, h - (int64_t)dy_range[1]);
     if (dtype != KB_F32) {
         const int stride = (int)table_stride(n_img);
         hipLaunchKernelGGL(inv_scale_kernel, dim3((stride + 63) / 64), dim3(64), 0, s, lp_scale,
@@ -604,15 +599,15 @@ kb_status launch_search(int fmt, int km, const StackView &v, hipStream_t s) {
 }
 
 kb_status launch_search_batch(int fmt, int km, const BatchJob *jobs, int n_jobs,
-                              int n_img_class, int k_cand, int generations, uint32_t *sync,
-                              int *grid, hipStream_t s) {
+                              int k_cand, int generations, uint32_t *sync, int *grid,
+                              hipStream_t s) {
     if (km_index(km) < 0)
         return fail(KB_EUNSUPPORTED, "no batched search compiled for list length %d", km);
     switch (fmt * kKmGroups + km_group(km)) {
 #define KB_GROUP(F, G)                                                                      \
     case F * kKmGroups + G:                                                                 \
-        return launch_search_batch_group<F, G>(km, jobs, n_jobs, n_img_class, k_cand,      \
-                                               generations, sync, grid, s);
+        return launch_search_batch_group<F, G>(km, jobs, n_jobs, k_cand, generations,      \
+                                               sync, grid, s);
 #define KB_FMT(F)                                                                    \
     KB_GROUP(F, 0) KB_GROUP(F, 1) KB_GROUP(F, 2) KB_GROUP(F, 3) KB_GROUP(F, 4)       \
     KB_GROUP(F, 5) KB_GROUP(F, 6) KB_GROUP(F, 7)
@@ -722,24 +717,12 @@ kb_status upload_tau_vel(const double *t, int64_t n_img, const double *vel, int6
 // visiting order into the workspace, asynchronously on `stream`.
 kb_status upload_table(const double *t, int64_t n_img, const double *vel, int64_t n_vel,
                        int64_t h, int64_t w, int64_t pix_bytes, void *workspace,
-                       hipStream_t stream, bool visiting_order, int32_t *dy_range) {
+                       hipStream_t stream, bool visiting_order) {
     const size_t tb = table_bytes(n_img, n_vel);
     std::vector<char> host(tb + static_cast<size_t>(n_vel) * sizeof(int32_t));
-    const GatherEntry *tab = reinterpret_cast<const GatherEntry *>(host.data());
     gather_table(t, n_img, vel, n_vel, h, w, pix_bytes, visiting_order,
                  reinterpret_cast<GatherEntry *>(host.data()),
                  reinterpret_cast<int32_t *>(host.data() + tb));
-    if (dy_range) {
-        const int64_t stride = table_stride(n_img);
-        int32_t lo = 0, hi = 0;
-        for (int64_t j = 0; j < n_vel; ++j)
-            for (int64_t i = 0; i < n_img; ++i) {
-                lo = std::min(lo, tab[j * stride + i].dy);
-                hi = std::max(hi, tab[j * stride + i].dy);
-            }
-        dy_range[0] = lo;
-        dy_range[1] = hi;
-    }
     // The order follows the (256-byte rounded) table directly in the workspace.
     return staged_copy(workspace, host.data(), host.size(), stream);
 }
@@ -858,12 +841,10 @@ kb_status kb_search(const void *planes, int32_t dtype, const float *lp_scale, in
     if (workspace_bytes < ws_need)
         return fail(KB_ENOMEM, "workspace needs %zu bytes (got %zu)", ws_need, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    int32_t dy_range[2] = {0, 0};
-    st = upload_table(t, n_img, vel, n_vel, h, w, dtype == KB_F32 ? 8 : 4, workspace, s, true,
-                      dy_range);
+    st = upload_table(t, n_img, vel, n_vel, h, w, dtype == KB_F32 ? 8 : 4, workspace, s);
     if (st != KB_OK) return st;
     return launch_search_in(planes, dtype, lp_scale, n_img, h, w, n_vel, k_cand, cand_nu,
-                            cand_alpha, cand_vel, cand_nobs, workspace, dy_range, s);
+                            cand_alpha, cand_vel, cand_nobs, workspace, s);
 }
 
 kb_status kb_topk(const float *psi_phi_f32, int64_t n_img, int64_t h, int64_t w,
@@ -1024,7 +1005,7 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
             if (image_class(jobs[q].n_img) == c) launch_order.push_back((int)q);
         count[c] = (int)launch_order.size() - first[c];
         if (count[c] > 0) {
-            kb_status st = launch_search_batch(dtype, km, nullptr, 0, c, kc, 0, nullptr,
+            kb_status st = launch_search_batch(dtype, km, nullptr, 0, kc, 0, nullptr,
                                                &grid[c], s);
             if (st != KB_OK) return st;
         }
@@ -1058,17 +1039,17 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
             d.nseg = (int)((j.w + 63) / 64);
             d.strip = d.nseg < KBMI_STRIP_TILES ? d.nseg : KBMI_STRIP_TILES;
             const int64_t tiles = (int64_t)d.nseg * j.h;
-            const bool block = KBMI_PERSIST_BS > 0 && dtype == KB_F32 &&
+            const bool block = dtype == KB_F32 &&
                                (g / 8) % KBMI_PERSIST_BS == 0 && tiles >= 4 * (int64_t)g;
             d.dense = block ? 0 : 1;
-            d.bs = KBMI_PERSIST_BS > 0 ? KBMI_PERSIST_BS : 1;
+            d.bs = KBMI_PERSIST_BS;
             d.brows = (g / 8) / d.bs;
             d.nbc = (d.nseg + d.bs - 1) / d.bs;
             d.nbr = (d.h + d.brows - 1) / d.brows;
             if (block) {
                 cursor = (cursor + g - 1) / g * g;
                 d.item_begin = (int)std::min<int64_t>(cursor, 2147483647LL);
-                cursor += (int64_t)((d.nbc + 7) / 8) * d.nbr * g;
+                cursor += (int64_t)block_generations(d.nbc, d.nbr) * g;
             } else {
                 d.item_begin = (int)std::min<int64_t>(cursor, 2147483647LL);
                 cursor += tiles;
@@ -1094,7 +1075,7 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
         if (count[c] == 0) continue;
         const BatchJob *dj = reinterpret_cast<const BatchJob *>(ws) + first[c];
         uint32_t *sync = reinterpret_cast<uint32_t *>(ws + lay.sync) + 8 * c;
-        kb_status st = launch_search_batch(dtype, km, dj, count[c], c, kc, (int)gens[c], sync,
+        kb_status st = launch_search_batch(dtype, km, dj, count[c], kc, (int)gens[c], sync,
                                            &grid[c], s);
         if (st != KB_OK) return st;
     }

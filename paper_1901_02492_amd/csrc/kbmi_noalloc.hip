@@ -215,10 +215,8 @@ kb_status kb_search_noalloc(const void *planes, int32_t dtype, const float *lp_s
                        reinterpret_cast<GatherEntry *>(ws + lay.table));
     st = launch_status("table_kernel");
     if (st != KB_OK) return st;
-    int32_t dy_range[2];
-    dy_extent(t, n_img, vel, n_vel, h, dy_range);
     return launch_search_in(planes, dtype, lp_scale, n_img, h, w, n_vel, k_cand, cand_nu,
-                            cand_alpha, cand_vel, cand_nobs, ws, dy_range, s);
+                            cand_alpha, cand_vel, cand_nobs, ws, s);
 }
 
 }  // extern "C"

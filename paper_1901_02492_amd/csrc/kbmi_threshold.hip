@@ -25,19 +25,17 @@
 namespace kbmi {
 namespace {
 
-constexpr int TH_NB = 16;          // table entries per batch (the table stride unit)
+constexpr int TH_NV = 16;          // loads of a batch
 constexpr int TH_STRIP = 4;        // tiles per strip of the tile order
 
-#ifndef KBMI_TH_PERSIST
-#define KBMI_TH_PERSIST 1   // threshold search: paced persistent order (float32 search's)
+#ifndef KBMI_TH_PER_CU
+#define KBMI_TH_PER_CU KBMI_PERSIST_PER_CU
 #endif
-
 // One tile: 64 adjacent start pixels of one row, every velocity, with the
 // top-k search's gathers (visit_velocities); each trajectory is scored and
 // appended if nu >= nu_min: one atomic per wave reserves the wave's slots.
-template <bool MB, bool INTERIOR>
 __device__ __forceinline__ void threshold_tile(
-    const float2 *__restrict__ planes, int n_img, int h, int w,
+    uint32_t *lds, const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, int row, int seg, float nu_min, kb_hit *__restrict__ hits, uint64_t cap,
     unsigned long long *__restrict__ n_hits) {
@@ -68,50 +66,42 @@ __device__ __forceinline__ void threshold_tile(
             }
         }
     };
-    visit_velocities<TH_NB, KB_F32, true, true, MB, INTERIOR, false>(
-        nullptr, planes, nullptr, n_img, h, w, disp, disp_stride, vel_index, n_vel, row, seg,
-        finish);
+    visit_velocities<KB_F32, TH_NV>(lds, planes, nullptr, n_img, h, w, disp, disp_stride,
+                                    vel_index, n_vel, row, seg, finish, []() { return false; },
+                                    []() {});
 }
 
 // Strip tile order, one wave per tile.
-template <bool MB>
 __global__ __launch_bounds__(64) void search_threshold_kernel(
     const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, int nseg, int ntiles, float nu_min, kb_hit *__restrict__ hits, uint64_t cap,
-    unsigned long long *__restrict__ n_hits, int row_lo, int row_hi) {
+    unsigned long long *__restrict__ n_hits) {
+    __shared__ uint32_t lds[kVisitWords];
     int row, seg;
     strip_tile(xcd_remap((int)blockIdx.x, ntiles), nseg, h, TH_STRIP, row, seg);
-    if (KBMI_INTERIOR && row >= row_lo && row < row_hi)
-        threshold_tile<MB, true>(planes, n_img, h, w, disp, disp_stride, vel_index, n_vel, row,
-                                 seg, nu_min, hits, cap, n_hits);
-    else
-        threshold_tile<MB, false>(planes, n_img, h, w, disp, disp_stride, vel_index, n_vel, row,
-                                  seg, nu_min, hits, cap, n_hits);
+    threshold_tile(lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel, row, seg,
+                   nu_min, hits, cap, n_hits);
 }
 
 // The paced persistent order of the float32 top-k search: per generation each
 // XCD covers one block of start pixels and its waves wait (a bounded time) for
 // each other at the end of the generation, so that their gathers share the
 // XCD's L2.  The wait only shapes timing.
-template <bool MB>
 __global__ __launch_bounds__(64) void search_threshold_persistent_kernel(
     const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, PersistMap pm, float nu_min, kb_hit *__restrict__ hits, uint64_t cap,
-    unsigned long long *__restrict__ n_hits, uint32_t *sync, int row_lo, int row_hi) {
+    unsigned long long *__restrict__ n_hits, uint32_t *sync) {
+    __shared__ uint32_t lds[kVisitWords];
     uint32_t *xcd_count = sync + (blockIdx.x & 7);
     const uint32_t per_xcd = gridDim.x >> 3;
     int spin = pm.spin;
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
         if (pm.map(gen, (int)blockIdx.x, row, seg)) {
-            if (KBMI_INTERIOR && row >= row_lo && row < row_hi)
-                threshold_tile<MB, true>(planes, n_img, h, w, disp, disp_stride, vel_index,
-                                         n_vel, row, seg, nu_min, hits, cap, n_hits);
-            else
-                threshold_tile<MB, false>(planes, n_img, h, w, disp, disp_stride, vel_index,
-                                          n_vel, row, seg, nu_min, hits, cap, n_hits);
+            threshold_tile(lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel, row, seg,
+                           nu_min, hits, cap, n_hits);
         }
         if (threadIdx.x == 0)
             __hip_atomic_fetch_add(xcd_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -127,7 +117,6 @@ __global__ __launch_bounds__(64) void search_threshold_persistent_kernel(
     }
 }
 
-template <bool MB>
 int threshold_grid() {
     static int cached[64] = {};
     int dev = 0;
@@ -135,10 +124,10 @@ int threshold_grid() {
     if (cached[dev] == 0) {
         int per_cu = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, search_threshold_persistent_kernel<MB>, 64, 0) != hipSuccess ||
+                &per_cu, search_threshold_persistent_kernel, 64, 0) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
-        cached[dev] = std::min(per_cu, KBMI_PERSIST_PER_CU) * cus;
+        cached[dev] = std::min(per_cu, KBMI_TH_PER_CU) * cus;
     }
     return cached[dev];
 }
@@ -440,16 +429,14 @@ ClusterLayout cluster_layout(int64_t n_hits, int64_t n_vel) {
     return l;
 }
 
-template <bool MB>
 kb_status launch_threshold(const float *psi_phi, int64_t n_img, int64_t h, int64_t w,
                            int64_t n_vel, float nu_min, kb_hit *hits, int64_t max_hits,
-                           uint64_t *n_hits, void *workspace, int row_lo, int row_hi,
-                           hipStream_t s) {
+                           uint64_t *n_hits, void *workspace, hipStream_t s) {
     char *ws = static_cast<char *>(workspace);
     const WorkspaceLayout lay = workspace_layout(n_img, h, w, n_vel);
     const int nseg = (int)((w + 63) / 64);
     const int64_t ntiles = (int64_t)nseg * h;
-    const int grid = KBMI_TH_PERSIST ? threshold_grid<MB>() : 0;
+    const int grid = threshold_grid();
     const int per_xcd = grid / 8;
     const GatherEntry *disp = reinterpret_cast<const GatherEntry *>(ws + lay.table);
     const int32_t *order = reinterpret_cast<const int32_t *>(ws + lay.order);
@@ -462,24 +449,24 @@ kb_status launch_threshold(const float *psi_phi, int64_t n_img, int64_t h, int64
         pm.brows = per_xcd / KBMI_PERSIST_BS;
         pm.nbc = (nseg + pm.bs - 1) / pm.bs;
         pm.nbr = ((int)h + pm.brows - 1) / pm.brows;
-        pm.generations = (pm.nbc + 7) / 8 * pm.nbr;
+        pm.generations = block_generations(pm.nbc, pm.nbr);
         pm.spin = KBMI_PERSIST_SPIN;
         uint32_t *sync = reinterpret_cast<uint32_t *>(ws + lay.sync);
         hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, sync, 8);
         kb_status st = launch_status("zero_words_kernel");
         if (st != KB_OK) return st;
-        hipLaunchKernelGGL(search_threshold_persistent_kernel<MB>, dim3((unsigned)grid), dim3(64),
+        hipLaunchKernelGGL(search_threshold_persistent_kernel, dim3((unsigned)grid), dim3(64),
                            0, s, reinterpret_cast<const float2 *>(psi_phi), (int)n_img, (int)h,
                            (int)w, disp, (int)table_stride(n_img), order, (int)n_vel, pm, nu_min,
                            hits, (uint64_t)max_hits,
-                           reinterpret_cast<unsigned long long *>(n_hits), sync, row_lo, row_hi);
+                           reinterpret_cast<unsigned long long *>(n_hits), sync);
         return launch_status("search_threshold_persistent_kernel");
     }
-    hipLaunchKernelGGL(search_threshold_kernel<MB>, dim3((unsigned)ntiles), dim3(64), 0, s,
+    hipLaunchKernelGGL(search_threshold_kernel, dim3((unsigned)ntiles), dim3(64), 0, s,
                        reinterpret_cast<const float2 *>(psi_phi), (int)n_img, (int)h, (int)w,
                        disp, (int)table_stride(n_img), order, (int)n_vel, nseg, (int)ntiles,
                        nu_min, hits, (uint64_t)max_hits,
-                       reinterpret_cast<unsigned long long *>(n_hits), row_lo, row_hi);
+                       reinterpret_cast<unsigned long long *>(n_hits));
     return launch_status("search_threshold_kernel");
 }
 
@@ -515,21 +502,14 @@ kb_status kb_search_threshold(const float *psi_phi, int64_t n_img, int64_t h, in
     if (workspace_bytes < lay.total)
         return fail(KB_ENOMEM, "workspace needs %zu bytes (got %zu)", lay.total, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    int32_t dy_range[2] = {0, 0};
-    st = upload_table(t, n_img, vel, n_vel, h, w, 8, workspace, s, true, dy_range);
+    st = upload_table(t, n_img, vel, n_vel, h, w, 8, workspace, s);
     if (st != KB_OK) return st;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s,
                        reinterpret_cast<unsigned long long *>(n_hits));
     st = launch_status("zero_u64_kernel");
     if (st != KB_OK) return st;
-    // Start rows whose displaced rows are all inside the frame.
-    const int row_lo = (int)std::min<int64_t>(h, -(int64_t)dy_range[0]);
-    const int row_hi = (int)std::max<int64_t>(0, h - (int64_t)dy_range[1]);
-    return n_img > TH_NB
-               ? launch_threshold<true>(psi_phi, n_img, h, w, n_vel, nu_min, hits, max_hits,
-                                        n_hits, workspace, row_lo, row_hi, s)
-               : launch_threshold<false>(psi_phi, n_img, h, w, n_vel, nu_min, hits, max_hits,
-                                         n_hits, workspace, row_lo, row_hi, s);
+    return launch_threshold(psi_phi, n_img, h, w, n_vel, nu_min, hits, max_hits, n_hits,
+                            workspace, s);
 }
 
 size_t kb_cluster_workspace_bytes(int64_t n_hits, int64_t n_vel) {

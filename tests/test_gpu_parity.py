@@ -80,6 +80,39 @@ def test_random_stacks(torch_dev, case):
     _full_check(torch_dev, s, k_cand=kc, k=k)
 
 
+# seed, n, n_vel, k: batches of one part (up to 17 images) and of several, in
+# one list (34 images and more), velocity chunks of 256 with a rest, lists with
+# each batch limit; 66 images: 16-bit planes without classes.
+CLASS_CASES = [(31, 2, 40, 5), (32, 16, 257, 50), (33, 17, 120, 20), (34, 18, 256, 64),
+               (35, 26, 300, 50), (36, 34, 90, 60), (37, 40, 100, 64), (38, 66, 60, 16)]
+
+
+@pytest.mark.parametrize("lp", [None, "f16"])
+@pytest.mark.parametrize("case", CLASS_CASES, ids=[f"n{c[1]}k{c[3]}" for c in CLASS_CASES])
+def test_velocities_seen_in_any_number_of_images(torch_dev, case, lp):
+    """Trajectories that leave the frame on every side after any number of
+    images (none and all included), on two tiles of which one is partial."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    seed, n, nv, k = case
+    h, w = 21, 91
+    s = synth.random_stack(seed, n=n, h=h, w=w, n_vel=nv, k=k, psf_size=5, vmax=130.0)
+    s.vel[::3] *= 0.05
+    _say(f"case classes N={n} V={nv} k={k} lp={lp}")
+    if lp is None:
+        _full_check(torch_dev, s, k=k)
+        return
+    ref = oracle.search(s.img, s.var, s.mask, s.t, s.psf, s.vel, k)
+    ref["all_Sabs"] = oracle.trajectory_sums(
+        np.abs(ref["psi"]), ref["phi"], oracle.validity(s.img, s.var, s.mask),
+        oracle.displacements(s.t, s.vel))[0]
+    img, var, mask = (torch.from_numpy(a).to("cuda:0") for a in (s.img, s.var, s.mask))
+    _, src, sc = lib.make_psi_phi(img, var, mask, s.psf, lp=lp)
+    cand = lib.search(src, s.t, s.vel, k, lp_scale=sc)
+    torch.cuda.synchronize()
+    parity.check_lp_candidates(parity.to_numpy(cand), s, ref, lp, k)
+
+
 def test_persistent_order_ragged_frame(torch_dev):
     """A frame large enough for the persistent tile order (several generations
     of blocks at K' = 50) with a ragged width and height, so that blocks
