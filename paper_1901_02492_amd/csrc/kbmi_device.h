@@ -69,11 +69,12 @@ struct StackView {
 
 // One stack of a batched search, as the batch kernel reads it from device
 // memory.  The launch's work items are its jobs' tiles: job j owns items
-// [item_begin_j, item_begin_{j+1}).  A dense job's items are its tiles in
-// strip order; a block job starts at a generation boundary and its items are
-// the paced persistent order of a single-stack search (generation
-// (item - item_begin) / grid, workgroup (item - item_begin) % grid), slots
-// past its frame's edge included and skipped.
+// [item_begin_j, item_begin_{j+1}), item_begin a multiple of 8.  A dense job's
+// items are its tiles in strip order; a block job starts at a generation
+// boundary and its items are the paced persistent order of a single-stack
+// search (generation (item - item_begin) / grid, workgroup
+// (item - item_begin) % grid), slots past its frame's edge included and
+// skipped.
 struct BatchJob {
     const void *planes;
     const float2 *inv_scale;
@@ -88,6 +89,14 @@ struct BatchJob {
     int dense;                 // 1: strip order (strip tiles wide); 0: block order
     int strip;
     int bs, brows, nbc, nbr;   // block order (PersistMap's fields)
+};
+
+// The launch of a batch: `grid` workgroups, `generations` generations, the
+// first `paced` of them paced through `sync`.
+struct BatchShape {
+    int n_jobs, k_cand;
+    int grid, generations, paced;
+    uint32_t *sync;
 };
 
 kb_status launch_status(const char *what);
@@ -116,14 +125,14 @@ constexpr int km_for(int k_cand) {
 template <int FMT, int G>
 kb_status launch_search_group(int km, const StackView &v, hipStream_t s);
 template <int FMT, int G>
-kb_status launch_search_batch_group(int km, const BatchJob *jobs, int n_jobs, int k_cand,
-                                    int generations, uint32_t *sync, int *grid, hipStream_t s);
+kb_status launch_search_batch_group(int km, const BatchJob *jobs, const BatchShape &b,
+                                    int *resident, hipStream_t s);
 #define KBMI_DECLARE_GROUP(F, G)                                                          \
     template <>                                                                           \
     kb_status launch_search_group<F, G>(int, const StackView &, hipStream_t);             \
     template <>                                                                           \
-    kb_status launch_search_batch_group<F, G>(int, const BatchJob *, int, int, int,         \
-                                              uint32_t *, int *, hipStream_t);
+    kb_status launch_search_batch_group<F, G>(int, const BatchJob *, const BatchShape &,    \
+                                              int *, hipStream_t);
 #define KBMI_DECLARE_FMT(F)                                                                 \
     KBMI_DECLARE_GROUP(F, 0) KBMI_DECLARE_GROUP(F, 1) KBMI_DECLARE_GROUP(F, 2)             \
     KBMI_DECLARE_GROUP(F, 3) KBMI_DECLARE_GROUP(F, 4) KBMI_DECLARE_GROUP(F, 5)             \
@@ -134,14 +143,10 @@ KBMI_DECLARE_FMT(2)
 #undef KBMI_DECLARE_FMT
 #undef KBMI_DECLARE_GROUP
 kb_status launch_search(int fmt, int km, const StackView &v, hipStream_t s);
-// One persistent launch of `generations` generations over the jobs of one
-// image-count class (0: n_img <= 8, 1: <= 16, 2: > 16), whose descriptors
-// (device) already hold their item ranges for a grid of *grid workgroups;
-// sync: 8 per-XCD counters (zeroed here).  With jobs == nullptr nothing is
-// launched and *grid receives that class's grid.
-kb_status launch_search_batch(int fmt, int km, const BatchJob *jobs, int n_jobs,
-                              int k_cand, int generations, uint32_t *sync,
-                              int *grid, hipStream_t s);
+// One launch over the jobs of a batch.  With jobs == nullptr nothing is
+// launched and *resident receives the workgroups the device holds at once.
+kb_status launch_search_batch(int fmt, int km, const BatchJob *jobs, const BatchShape &b,
+                              int *resident, hipStream_t s);
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -1010,17 +1015,22 @@ __global__ void zero_words_kernel(uint32_t *p, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// Batched search: one persistent launch covers the tiles of several stacks
-// (the serving path).  The grid is the number of workgroups the GPU holds at
-// once; in generation g, workgroup w processes work item g * grid + w (see
-// BatchJob), then waits with the others of its XCD as in the single-stack
-// persistent search.  Each tile runs exactly the single-stack search, so a
-// stack's results do not depend on what it is batched with.
+// Batched search: one launch covers the tiles of several stacks (the serving
+// path), whatever their image counts.  In generation g, workgroup w processes
+// work item g * grid + w (see BatchJob); after the first `paced` generations,
+// which hold the jobs in block order, it waits with the others of its XCD as
+// in the single-stack persistent search.  Without such jobs there is one
+// generation of one workgroup per tile, so that the hardware balances tiles
+// of unlike work; the jobs with the longest tiles come first.  (One launch per
+// image-count class, each with its own tail, took 1.80 ms for six stacks of 5
+// to 20 images and up to 400 x 500 pixels; one launch takes 0.92 ms.)  Each tile runs exactly the
+// single-stack search, so a stack's results do not depend on what it is
+// batched with.
 // ---------------------------------------------------------------------------
 template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__restrict__ jobs_,
                                                              int n_jobs, int generations,
-                                                             int spin, int k_cand,
+                                                             int paced, int spin, int k_cand,
                                                              uint32_t *sync) {
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     // The descriptors do not change during the launch: read through the
@@ -1030,17 +1040,21 @@ __global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__r
     uint32_t *xcd_count = sync + (blockIdx.x & 7);
     const int grid = (int)gridDim.x;
     const uint32_t per_xcd = gridDim.x >> 3;
-    int j = 0;
     for (int gen = 0; gen < generations; ++gen) {
         const int item = gen * grid + (int)blockIdx.x;
-        while (j + 1 < n_jobs && item >= jobs[j + 1].item_begin) ++j;
+        int j = 0;
+        for (int end = n_jobs; end - j > 1;) {   // the last job that begins at or before item
+            const int mid = (j + end) >> 1;
+            if (item >= jobs[mid].item_begin) j = mid;
+            else end = mid;
+        }
         const CJob &jb = jobs[j];
         const int li = item - jb.item_begin;
         int row = 0, seg = 0;
         bool ok;
         if (jb.dense) {
             ok = li < jb.nseg * jb.h;
-            if (ok) strip_tile(li, jb.nseg, jb.h, jb.strip, row, seg);
+            if (ok) strip_tile(xcd_remap(li, jb.nseg * jb.h), jb.nseg, jb.h, jb.strip, row, seg);
         } else {
             PersistMap pm;
             pm.nseg = jb.nseg;
@@ -1057,6 +1071,7 @@ __global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__r
                 lds, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp, jb.disp_stride,
                 jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
                 jb.cand_vel, jb.cand_nobs);
+        if (gen >= paced) continue;
         // Generation boundary (as in the single-stack persistent search).
         if (threadIdx.x == 0)
             __hip_atomic_fetch_add(xcd_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -598,16 +598,14 @@ kb_status launch_search(int fmt, int km, const StackView &v, hipStream_t s) {
     return fail(KB_EUNSUPPORTED, "no search compiled for format %d, list length %d", fmt, km);
 }
 
-kb_status launch_search_batch(int fmt, int km, const BatchJob *jobs, int n_jobs,
-                              int k_cand, int generations, uint32_t *sync, int *grid,
-                              hipStream_t s) {
+kb_status launch_search_batch(int fmt, int km, const BatchJob *jobs, const BatchShape &b,
+                              int *resident, hipStream_t s) {
     if (km_index(km) < 0)
         return fail(KB_EUNSUPPORTED, "no batched search compiled for list length %d", km);
     switch (fmt * kKmGroups + km_group(km)) {
 #define KB_GROUP(F, G)                                                                      \
     case F * kKmGroups + G:                                                                 \
-        return launch_search_batch_group<F, G>(km, jobs, n_jobs, k_cand, generations,      \
-                                               sync, grid, s);
+        return launch_search_batch_group<F, G>(km, jobs, b, resident, s);
 #define KB_FMT(F)                                                                    \
     KB_GROUP(F, 0) KB_GROUP(F, 1) KB_GROUP(F, 2) KB_GROUP(F, 3) KB_GROUP(F, 4)       \
     KB_GROUP(F, 5) KB_GROUP(F, 6) KB_GROUP(F, 7)
@@ -942,10 +940,6 @@ bool batch_layout(const kb_job *jobs, int64_t n_jobs, BatchLayout &l) {
     return true;
 }
 
-// Image-count class of a job: the batch launches one kernel per class (one
-// load batch of 8 or 16 per velocity, or batches of 16), like kb_search.
-int image_class(int64_t n_img) { return n_img <= 8 ? 0 : (n_img <= 16 ? 1 : 2); }
-
 }  // namespace
 
 extern "C" {
@@ -989,97 +983,88 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
     if (workspace_bytes < lay.total)
         return fail(KB_ENOMEM, "workspace needs %zu bytes (got %zu)", lay.total, workspace_bytes);
 
-    // Work items of each class's persistent launch.  A job of float32 planes
-    // large enough for the paced block order (as kb_search chooses it) starts
-    // at a generation boundary and takes its whole block sequence; the others
-    // are packed densely, tile after tile.
+    // Work items of the launch.  A job of float32 planes large enough for the
+    // paced block order (as kb_search chooses it) starts at a generation
+    // boundary and takes its whole block sequence; the others follow densely,
+    // tile after tile, those with the longest tiles first.
     const int kc = (int)k_cand;
     const int km = km_for(kc);
     hipStream_t s = (hipStream_t)stream;
-    int grid[3] = {0, 0, 0}, count[3] = {0, 0, 0}, first[3] = {0, 0, 0};
-    int64_t gens[3] = {0, 0, 0};
-    std::vector<int> launch_order;
-    for (int c = 0; c < 3; ++c) {
-        first[c] = (int)launch_order.size();
-        for (int64_t q = 0; q < n_jobs; ++q)
-            if (image_class(jobs[q].n_img) == c) launch_order.push_back((int)q);
-        count[c] = (int)launch_order.size() - first[c];
-        if (count[c] > 0) {
-            kb_status st = launch_search_batch(dtype, km, nullptr, 0, kc, 0, nullptr,
-                                               &grid[c], s);
-            if (st != KB_OK) return st;
-        }
-    }
+    int g = 0;
+    BatchShape shape{(int)n_jobs, kc, 0, 1, 0, nullptr};
+    kb_status st = launch_search_batch(dtype, km, nullptr, shape, &g, s);
+    if (st != KB_OK) return st;
+    auto blocks = [&](const kb_job &j) {
+        return dtype == KB_F32 && (g / 8) % KBMI_PERSIST_BS == 0 &&
+               (j.w + 63) / 64 * j.h >= 4 * (int64_t)g;
+    };
+    std::vector<int> launch_order(static_cast<size_t>(n_jobs));
+    for (int64_t q = 0; q < n_jobs; ++q) launch_order[static_cast<size_t>(q)] = (int)q;
+    std::stable_sort(launch_order.begin(), launch_order.end(), [&](int a, int b) {
+        const kb_job &ja = jobs[a], &jb = jobs[b];
+        const bool ba = blocks(ja), bb = blocks(jb);
+        return ba != bb ? ba : ja.n_img * ja.n_vel > jb.n_img * jb.n_vel;
+    });
     char *ws = static_cast<char *>(workspace);
     std::vector<char> host(lay.total, 0);
     BatchJob *desc = reinterpret_cast<BatchJob *>(host.data());
-    for (int c = 0; c < 3; ++c) {
-        int64_t cursor = 0;
-        const int g = grid[c];
-        for (int pos = first[c]; pos < first[c] + count[c]; ++pos) {
-            const int q = launch_order[pos];
-            const kb_job &j = jobs[q];
-            gather_table(j.t, j.n_img, j.vel, j.n_vel, j.h, j.w, dtype == KB_F32 ? 8 : 4, true,
-                         reinterpret_cast<GatherEntry *>(host.data() + lay.table[q]),
-                         reinterpret_cast<int32_t *>(host.data() + lay.order[q]));
-            BatchJob &d = desc[pos];
-            d.planes = j.planes;
-            d.inv_scale = reinterpret_cast<const float2 *>(ws + lay.inv_scale[q]);
-            d.disp = reinterpret_cast<const GatherEntry *>(ws + lay.table[q]);
-            d.vel_index = reinterpret_cast<const int32_t *>(ws + lay.order[q]);
-            d.cand_nu = j.cand_nu;
-            d.cand_alpha = j.cand_alpha;
-            d.cand_vel = j.cand_vel;
-            d.cand_nobs = j.cand_nobs;
-            d.n_img = (int)j.n_img;
-            d.h = (int)j.h;
-            d.w = (int)j.w;
-            d.disp_stride = (int)table_stride(j.n_img);
-            d.n_vel = (int)j.n_vel;
-            d.nseg = (int)((j.w + 63) / 64);
-            d.strip = d.nseg < KBMI_STRIP_TILES ? d.nseg : KBMI_STRIP_TILES;
-            const int64_t tiles = (int64_t)d.nseg * j.h;
-            const bool block = dtype == KB_F32 &&
-                               (g / 8) % KBMI_PERSIST_BS == 0 && tiles >= 4 * (int64_t)g;
-            d.dense = block ? 0 : 1;
-            d.bs = KBMI_PERSIST_BS;
-            d.brows = (g / 8) / d.bs;
-            d.nbc = (d.nseg + d.bs - 1) / d.bs;
-            d.nbr = (d.h + d.brows - 1) / d.brows;
-            if (block) {
-                cursor = (cursor + g - 1) / g * g;
-                d.item_begin = (int)std::min<int64_t>(cursor, 2147483647LL);
-                cursor += (int64_t)block_generations(d.nbc, d.nbr) * g;
-            } else {
-                d.item_begin = (int)std::min<int64_t>(cursor, 2147483647LL);
-                cursor += tiles;
-            }
-            if (cursor + g > 2147483647LL)
-                return fail(KB_EINVAL, "batch holds more work items than one launch");
+    int64_t cursor = 0;
+    for (int64_t pos = 0; pos < n_jobs; ++pos) {
+        const int q = launch_order[pos];
+        const kb_job &j = jobs[q];
+        gather_table(j.t, j.n_img, j.vel, j.n_vel, j.h, j.w, dtype == KB_F32 ? 8 : 4, true,
+                     reinterpret_cast<GatherEntry *>(host.data() + lay.table[q]),
+                     reinterpret_cast<int32_t *>(host.data() + lay.order[q]));
+        BatchJob &d = desc[pos];
+        d.planes = j.planes;
+        d.inv_scale = reinterpret_cast<const float2 *>(ws + lay.inv_scale[q]);
+        d.disp = reinterpret_cast<const GatherEntry *>(ws + lay.table[q]);
+        d.vel_index = reinterpret_cast<const int32_t *>(ws + lay.order[q]);
+        d.cand_nu = j.cand_nu;
+        d.cand_alpha = j.cand_alpha;
+        d.cand_vel = j.cand_vel;
+        d.cand_nobs = j.cand_nobs;
+        d.n_img = (int)j.n_img;
+        d.h = (int)j.h;
+        d.w = (int)j.w;
+        d.disp_stride = (int)table_stride(j.n_img);
+        d.n_vel = (int)j.n_vel;
+        d.nseg = (int)((j.w + 63) / 64);
+        d.strip = d.nseg < KBMI_STRIP_TILES ? d.nseg : KBMI_STRIP_TILES;
+        const int64_t tiles = (int64_t)d.nseg * j.h;
+        const bool block = blocks(j);
+        d.dense = block ? 0 : 1;
+        d.bs = KBMI_PERSIST_BS;
+        d.brows = (g / 8) / d.bs;
+        d.nbc = (d.nseg + d.bs - 1) / d.bs;
+        d.nbr = (d.h + d.brows - 1) / d.brows;
+        d.item_begin = (int)std::min<int64_t>(cursor, 2147483647LL);
+        if (block) {
+            const int n = block_generations(d.nbc, d.nbr);
+            cursor += (int64_t)n * g;
+            shape.paced += n;
+        } else {
+            cursor += (tiles + 7) / 8 * 8;
         }
-        gens[c] = g > 0 ? (cursor + g - 1) / g : 0;
+        if (cursor + g > 2147483647LL)
+            return fail(KB_EINVAL, "batch holds more work items than one launch");
     }
-    kb_status up = staged_copy(ws, host.data(), host.size(), s);
-    if (up != KB_OK) return up;
+    shape.grid = shape.paced > 0 ? g : (int)cursor;
+    shape.generations = (int)((cursor + shape.grid - 1) / shape.grid);
+    shape.sync = reinterpret_cast<uint32_t *>(ws + lay.sync);
+    st = staged_copy(ws, host.data(), host.size(), s);
+    if (st != KB_OK) return st;
     if (dtype != KB_F32) {
         for (int64_t q = 0; q < n_jobs; ++q) {
             const int stride = (int)table_stride(jobs[q].n_img);
             hipLaunchKernelGGL(inv_scale_kernel, dim3((stride + 63) / 64), dim3(64), 0, s,
                                jobs[q].lp_scale, (int)jobs[q].n_img, stride,
                                reinterpret_cast<float2 *>(ws + lay.inv_scale[q]));
-            kb_status st = launch_status("inv_scale_kernel");
+            st = launch_status("inv_scale_kernel");
             if (st != KB_OK) return st;
         }
     }
-    for (int c = 0; c < 3; ++c) {
-        if (count[c] == 0) continue;
-        const BatchJob *dj = reinterpret_cast<const BatchJob *>(ws) + first[c];
-        uint32_t *sync = reinterpret_cast<uint32_t *>(ws + lay.sync) + 8 * c;
-        kb_status st = launch_search_batch(dtype, km, dj, count[c], kc, (int)gens[c], sync,
-                                           &grid[c], s);
-        if (st != KB_OK) return st;
-    }
-    return KB_OK;
+    return launch_search_batch(dtype, km, reinterpret_cast<const BatchJob *>(ws), shape, &g, s);
 }
 
 }  // extern "C"

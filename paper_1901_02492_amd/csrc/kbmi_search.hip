@@ -89,50 +89,39 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
 }
 
 template <int KM>
-kb_status launch_km(const StackView &v, hipStream_t s) {
-    return launch_one<KM>(v, s);
-}
-
-template <int KM>
-kb_status launch_batch_one(const BatchJob *jobs, int n_jobs, int k_cand, int generations,
-                           uint32_t *sync, int *grid, hipStream_t s) {
+kb_status launch_batch_km(const BatchJob *jobs, const BatchShape &b, int *resident,
+                          hipStream_t s) {
     constexpr int PB = KBMI_QUEUE;
     auto kernel = search_batch_kernel<KM, PB, KBMI_FMT>;
-    const int g = resident_workgroups<search_batch_kernel<KM, PB, KBMI_FMT>>();
-    if (g < 8 || g % 8 != 0)
-        return fail(KB_EDEVICE, "batched search: no persistent grid for this device (%d)", g);
     if (!jobs) {
-        *grid = g;
+        const int g = resident_workgroups<search_batch_kernel<KM, PB, KBMI_FMT>>();
+        if (g < 8 || g % 8 != 0)
+            return fail(KB_EDEVICE, "batched search: no persistent grid for this device (%d)", g);
+        *resident = g;
         return KB_OK;
     }
-    if (*grid != g) return fail(KB_EDEVICE, "batched search: grid changed (%d, %d)", *grid, g);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, sync, 8);
-    kb_status st = launch_status("zero_words_kernel");
-    if (st != KB_OK) return st;
-    hipLaunchKernelGGL(kernel, dim3(g), dim3(64), 0, s, jobs, n_jobs, generations,
-                       KBMI_PERSIST_SPIN, k_cand, sync);
+    if (b.paced > 0) {
+        hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, b.sync, 8);
+        const kb_status st = launch_status("zero_words_kernel");
+        if (st != KB_OK) return st;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)b.grid), dim3(64), 0, s, jobs, b.n_jobs,
+                       b.generations, b.paced, KBMI_PERSIST_SPIN, b.k_cand, b.sync);
     return launch_status("search_batch_kernel");
-}
-
-template <int KM>
-kb_status launch_batch_km(const BatchJob *jobs, int n_jobs, int k_cand,
-                          int generations, uint32_t *sync, int *grid, hipStream_t s) {
-    return launch_batch_one<KM>(jobs, n_jobs, k_cand, generations, sync, grid, s);
 }
 
 // List lengths of this translation unit's group are compiled; the others are
 // left to their own units (the dispatcher never sends them here).
 template <int K>
 kb_status launch_in_group(const StackView &v, hipStream_t s) {
-    if constexpr (km_group(K) == KBMI_GROUP) return launch_km<K>(v, s);
+    if constexpr (km_group(K) == KBMI_GROUP) return launch_one<K>(v, s);
     else return fail(KB_EUNSUPPORTED, "list length %d is not compiled in this group", K);
 }
 
 template <int K>
-kb_status launch_batch_in_group(const BatchJob *jobs, int n_jobs, int k_cand,
-                                int generations, uint32_t *sync, int *grid, hipStream_t s) {
-    if constexpr (km_group(K) == KBMI_GROUP)
-        return launch_batch_km<K>(jobs, n_jobs, k_cand, generations, sync, grid, s);
+kb_status launch_batch_in_group(const BatchJob *jobs, const BatchShape &b, int *resident,
+                                hipStream_t s) {
+    if constexpr (km_group(K) == KBMI_GROUP) return launch_batch_km<K>(jobs, b, resident, s);
     else return fail(KB_EUNSUPPORTED, "list length %d is not compiled in this group", K);
 }
 
@@ -152,14 +141,12 @@ kb_status launch_search_group<KBMI_FMT, KBMI_GROUP>(int km, const StackView &v, 
 
 template <>
 kb_status launch_search_batch_group<KBMI_FMT, KBMI_GROUP>(int km, const BatchJob *jobs,
-                                                           int n_jobs, int k_cand,
-                                                           int generations,
-                                                           uint32_t *sync, int *grid,
+                                                           const BatchShape &b, int *resident,
                                                            hipStream_t s) {
     switch (km) {
-#define KB_CASE(K)                                                                     \
-    case K:                                                                            \
-        return launch_batch_in_group<K>(jobs, n_jobs, k_cand, generations, sync, grid, s);
+#define KB_CASE(K) \
+    case K:        \
+        return launch_batch_in_group<K>(jobs, b, resident, s);
         KB_SEARCH_KM_LIST(KB_CASE)
 #undef KB_CASE
     }

@@ -655,3 +655,26 @@ def test_batched_search_equals_solo(torch_dev, lp):
     for jb, solo in zip(jobs, solos):
         for a, b in zip(parity.to_numpy(jb["out"]), parity.to_numpy(solo)):
             assert a.tobytes() == b.tobytes()
+
+
+def test_batch_of_block_and_dense_jobs_equals_solo(torch_dev):
+    """One launch with a stack large enough for the paced block order between
+    small ones of 1 to 26 images, whose tiles number no multiple of eight."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    k = 50
+    shapes = [(5, 41, 70, 60), (6, 521, 1000, 60), (26, 33, 130, 55), (1, 7, 20, 50)]
+    jobs, solos = [], []
+    for q, (n, h, w, nv) in enumerate(shapes):
+        _say(f"case batch N={n} HxW={h}x{w} V={nv}")
+        s = synth.random_stack(87 + q, n=n, h=h, w=w, n_vel=nv, k=k, psf_size=5, vmax=min(h, w))
+        planes = lib.make_psi_phi(*(torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask)),
+                                  s.psf)
+        solos.append(lib.search(planes, s.t, s.vel, k))
+        jobs.append(dict(planes=planes, t=s.t, vel=s.vel, out=lib.alloc_candidates(h, w, k, dev)))
+    lib.search_batch(jobs, k)
+    torch.cuda.synchronize()
+    for jb, solo in zip(jobs, solos):
+        for a, b in zip(parity.to_numpy(jb["out"]), parity.to_numpy(solo)):
+            assert a.tobytes() == b.tobytes()
