@@ -48,100 +48,168 @@ struct PsfTaps {
 };
 
 constexpr int PP_TW = 64;       // output tile width
-constexpr int PP_TH = 16;       // output tile height
-constexpr int PP_THREADS = 256; // 4 waves; each thread produces 4 columns of one row
+constexpr int PP_TH = 16;       // output tile height for each row that a thread produces
+constexpr int PP_THREADS = 256; // 4 waves; each thread produces 4 columns of 1 or 2 rows
+constexpr int PP_BATCH = 4;     // staged pixels whose loads are in flight together
+// 64 x 32 tiles from which on a thread takes two rows: 20 x 2048^2 at 11 x 11 (40960
+// tiles) 1.150 -> 0.997 ms with the half-precision copy; 15 x 1024^2 at 15 x 15
+// (7680) 0.273 -> 0.278 and 20 x 512^2 at 11 x 11 (2560) 50.8 -> 57.6 us, where
+// the last round of fewer, longer workgroups leaves CUs idle.
+constexpr int64_t PP_MIN_TILES2 = 16384;
 // LDS of one tile with its halo for a PSF of ph rows and PW columns: the
 // (a, w) pairs, then the validity bytes (sized at launch, so a small PSF
 // leaves room for more resident workgroups).
 template <int PW>
-constexpr size_t psi_phi_lds_bytes(int ph) {
-    return (size_t)(PP_TH + ph - 1) * (size_t)(PP_TW + PW - 1) * (sizeof(float2) + 1);
+constexpr size_t psi_phi_lds_bytes(int ph, int rows) {
+    return (size_t)(PP_TH * rows + ph - 1) * (size_t)(PP_TW + PW - 1) * (sizeof(float2) + 1);
+}
+
+// im / vr and 1 / vr of a wave, correctly rounded: one reciprocal, refined
+// once, serves both quotients, each corrected with two fused residuals (12
+// instructions; two divisions of their own, with scaling and fix-up, take 26).
+// Where a lane's operands could need scaling, the wave divides in full.  (A
+// quotient of -0 comes out +0, which every sum it enters gives back too.)
+__device__ inline void divide_by_variance(float im, float vr, bool good, float &a, float &wt) {
+    const float m = fabsf(im);
+    const bool plain = vr >= 0x1p-60f && vr <= 0x1p60f && m <= 0x1p60f && (m >= 0x1p-60f || m == 0.f);
+    if (__any(good && !plain)) {
+        wt = 1.0f / vr;
+        a = im / vr;
+        return;
+    }
+    const float r0 = __builtin_amdgcn_rcpf(vr);
+    const float r = fmaf(fmaf(-vr, r0, 1.0f), r0, r0);
+    auto quotient = [&](float n, float q0) {
+        const float q1 = fmaf(fmaf(-vr, q0, n), r, q0);
+        return fmaf(fmaf(-vr, q1, n), r, q1);
+    };
+    wt = quotient(1.0f, r);
+    a = quotient(im, im * r);
 }
 
 // psi = a (x) T and phi = w (x) T^2 (cross-correlations with zero padding) for
-// one 64 x 16 output tile of one image, with a = valid * img / var and
+// one 64 x 16 ROWS output tile of one image, with a = valid * img / var and
 // w = valid / var staged in LDS for the tile plus its halo as interleaved
 // pairs.  The PSF width PW is a compile-time constant: each thread computes 4
-// adjacent columns of one output row and, per PSF row, reads the
+// adjacent columns of ROWS adjacent output rows and reads, per staged row, the
 // (4 + PW - 1)-pixel segment it needs once (16-byte LDS reads), so one LDS
-// read serves about three FMAs.  Per output the taps are summed row by row,
-// left to right.
-template <int PW>
+// read serves about three FMAs of each row.  Per output the taps are summed row
+// by row, left to right.
+//
+// FP32 issue bounds it (242 FMAs a pixel at 11 x 11: 0.52 ms for 20 x 2048^2).
+// Beside them, two rows a thread stage 1.5 pixels per output pixel where one
+// row stages 1.9 and reads each segment for one row only, the two divisions
+// share a reciprocal, and four staged pixels' loads are in flight together.
+// 20 x 2048^2, 11 x 11, with the half-precision copy (0.23 ms of it): 1.210 -> 0.997
+// ms; 15 x 1024^2, 15 x 15, bfloat16 copy 0.283 -> 0.273; 20 x 512^2, 11 x 11 55.5
+// -> 50.8 us.  (Squared taps from the host, a second row of scalar loads
+// beside each row of taps: 1.117 ms.)
+template <int PW, int ROWS>
 __global__ __launch_bounds__(PP_THREADS) void psi_phi_kernel(
     const float *__restrict__ img, const float *__restrict__ var,
     const uint8_t *__restrict__ mask, int h, int w, int ph, PsfTaps psf,
     float2 *__restrict__ out, uint32_t *__restrict__ maxabs) {
+    constexpr int TH = PP_TH * ROWS;
     constexpr int LW = PP_TW + PW - 1;        // staged columns (even: PW is odd)
-    constexpr int SEG = 4 + PW - 1;           // pixels one thread reads per PSF row
+    constexpr int SEG = 4 + PW - 1;           // pixels one thread reads per staged row
     static_assert(PW % 2 == 1 && LW % 2 == 0 && SEG % 2 == 0, "odd PSF widths only");
     extern __shared__ __align__(16) unsigned char pp_lds[];
     float2 *s_aw = reinterpret_cast<float2 *>(pp_lds);
-    uint8_t *s_ok = pp_lds + (size_t)(PP_TH + ph - 1) * LW * sizeof(float2);
+    uint8_t *s_ok = pp_lds + (size_t)(TH + ph - 1) * LW * sizeof(float2);
 
     const int i = blockIdx.z;
     const int tx0 = blockIdx.x * PP_TW;
-    const int ty0 = blockIdx.y * PP_TH;
+    const int ty0 = blockIdx.y * TH;
     const int cy = ph / 2, cx = PW / 2;
-    const int lh = PP_TH + ph - 1;
+    const int n_staged = (TH + ph - 1) * LW;
     const size_t plane = (size_t)i * (size_t)h * (size_t)w;
 
-    for (int idx = threadIdx.x; idx < lh * LW; idx += PP_THREADS) {
-        const int ly = idx / LW, lx = idx - ly * LW;
-        const int gy = ty0 + ly - cy, gx = tx0 + lx - cx;
-        float a = 0.f, wt = 0.f;
-        uint8_t ok = 0;
-        if (gy >= 0 && gy < h && gx >= 0 && gx < w) {
-            const size_t p = plane + (size_t)gy * w + gx;
-            const float im = img[p], vr = var[p];
-            const bool good = (mask == nullptr || mask[p] == 0) && isfinite(im) &&
-                              isfinite(vr) && vr > 0.f;
-            if (good) {
-                wt = 1.0f / vr;
-                a = im / vr;
-                ok = 1;
+    for (int i0 = threadIdx.x; i0 < n_staged; i0 += PP_BATCH * PP_THREADS) {
+        float im[PP_BATCH], vr[PP_BATCH];
+        bool good[PP_BATCH];
+#pragma unroll
+        for (int b = 0; b < PP_BATCH; ++b) {
+            const int idx = i0 + b * PP_THREADS;
+            const int ly = idx / LW, lx = idx - ly * LW;
+            const int gy = ty0 + ly - cy, gx = tx0 + lx - cx;
+            good[b] = idx < n_staged && gy >= 0 && gy < h && gx >= 0 && gx < w;
+            const size_t p = plane + (good[b] ? (size_t)gy * w + gx : 0);
+            im[b] = img[p];
+            vr[b] = var[p];
+            if (mask != nullptr) good[b] = good[b] && mask[p] == 0;
+        }
+#pragma unroll
+        for (int b = 0; b < PP_BATCH; ++b) {
+            const int idx = i0 + b * PP_THREADS;
+            good[b] = good[b] && isfinite(im[b]) && isfinite(vr[b]) && vr[b] > 0.f;
+            float a, wt;
+            divide_by_variance(im[b], vr[b], good[b], a, wt);
+            if (idx < n_staged) {
+                s_aw[idx] = good[b] ? make_float2(a, wt) : make_float2(0.f, 0.f);
+                s_ok[idx] = good[b] ? 1 : 0;
             }
         }
-        s_aw[idx] = make_float2(a, wt);
-        s_ok[idx] = ok;
     }
     __syncthreads();
 
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float ps[4] = {0.f, 0.f, 0.f, 0.f}, pf[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int u = 0; u < ph; ++u) {
-        const float4 *row = reinterpret_cast<const float4 *>(s_aw + (ty + u) * LW + 4 * tx);
-        float2 seg[SEG];
+    const int tx = threadIdx.x & 15, ty = (threadIdx.x >> 4) * ROWS;
+    float ps[ROWS][4] = {}, pf[ROWS][4] = {};
+    float2 seg[SEG];
+    auto read_row = [&](int l) {
+        const float4 *row = reinterpret_cast<const float4 *>(s_aw + (ty + l) * LW + 4 * tx);
 #pragma unroll
         for (int q = 0; q < SEG / 2; ++q) {
             const float4 x = row[q];
             seg[2 * q] = make_float2(x.x, x.y);
             seg[2 * q + 1] = make_float2(x.z, x.w);
         }
+    };
+    // Tap row u on the segment read, for the thread's output row r.
+    auto add_taps = [&](int u, int r) {
 #pragma unroll
         for (int v = 0; v < PW; ++v) {
             const float tv = psf.t[u * PW + v];
             const float t2 = tv * tv;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                ps[c] = fmaf(seg[c + v].x, tv, ps[c]);
-                pf[c] = fmaf(seg[c + v].y, t2, pf[c]);
+                ps[r][c] = fmaf(seg[c + v].x, tv, ps[r][c]);
+                pf[r][c] = fmaf(seg[c + v].y, t2, pf[r][c]);
             }
         }
+    };
+    if constexpr (ROWS == 1) {
+        for (int u = 0; u < ph; ++u) {
+            read_row(u);
+            add_taps(u, 0);
+        }
+    } else {
+        read_row(0);
+        add_taps(0, 0);
+        for (int u = 1; u < ph; ++u) {
+            read_row(u);
+            add_taps(u, 0);
+            add_taps(u - 1, 1);
+        }
+        read_row(ph);
+        add_taps(ph - 1, 1);
     }
-    const int gy = ty0 + ty;
     float mp = 0.f, mf = 0.f;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int gx = tx0 + 4 * tx + c;
-        if (gy < h && gx < w) {
-            float2 res = make_float2(0.f, 0.f);
-            if (s_ok[(ty + cy) * LW + 4 * tx + c + cx]) {
-                // phi >= 0 always; a valid pixel keeps a nonzero bit pattern.
-                res = make_float2(ps[c], pf[c] > 0.f ? pf[c] : -0.0f);
-                mp = fmaxf(mp, fabsf(ps[c]));
-                mf = fmaxf(mf, pf[c]);
+    for (int r = 0; r < ROWS; ++r) {
+        const int gy = ty0 + ty + r;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int gx = tx0 + 4 * tx + c;
+            if (gy < h && gx < w) {
+                float2 res = make_float2(0.f, 0.f);
+                if (s_ok[(ty + r + cy) * LW + 4 * tx + c + cx]) {
+                    // phi >= 0 always; a valid pixel keeps a nonzero bit pattern.
+                    res = make_float2(ps[r][c], pf[r][c] > 0.f ? pf[r][c] : -0.0f);
+                    mp = fmaxf(mp, fabsf(ps[r][c]));
+                    mf = fmaxf(mf, pf[r][c]);
+                }
+                out[plane + (size_t)gy * w + gx] = res;
             }
-            out[plane + (size_t)gy * w + gx] = res;
         }
     }
     if (maxabs != nullptr) {
@@ -784,7 +852,9 @@ kb_status kb_make_psi_phi(const float *img, const float *var, const uint8_t *mas
     }
     PsfTaps taps{};
     for (int64_t u = 0; u < psf_h * psf_w; ++u) taps.t[u] = psf[u];
-    const dim3 grid((unsigned)((w + PP_TW - 1) / PP_TW), (unsigned)((h + PP_TH - 1) / PP_TH),
+    const int64_t tiles_x = (w + PP_TW - 1) / PP_TW, tiles_y2 = (h + 2 * PP_TH - 1) / (2 * PP_TH);
+    const bool two = tiles_x * tiles_y2 * n_img >= PP_MIN_TILES2;
+    const dim3 grid((unsigned)tiles_x, (unsigned)(two ? tiles_y2 : (h + PP_TH - 1) / PP_TH),
                     (unsigned)n_img);
     hipStream_t s = (hipStream_t)stream;
     const bool lp = lp_dtype != KB_F32;
@@ -799,9 +869,9 @@ kb_status kb_make_psi_phi(const float *img, const float *var, const uint8_t *mas
     switch (psf_w) {
 #define KB_PSF_W(PW)                                                                         \
     case PW:                                                                                 \
-        hipLaunchKernelGGL(psi_phi_kernel<PW>, grid, dim3(PP_THREADS),                       \
-                           psi_phi_lds_bytes<PW>((int)psf_h), s, img, var, mask, (int)h,      \
-                           (int)w, (int)psf_h, taps, pp, maxabs);                           \
+        hipLaunchKernelGGL((two ? psi_phi_kernel<PW, 2> : psi_phi_kernel<PW, 1>), grid,       \
+                           dim3(PP_THREADS), psi_phi_lds_bytes<PW>((int)psf_h, two ? 2 : 1),  \
+                           s, img, var, mask, (int)h, (int)w, (int)psf_h, taps, pp, maxabs);  \
         break;
         KB_PSF_W(1) KB_PSF_W(3) KB_PSF_W(5) KB_PSF_W(7) KB_PSF_W(9) KB_PSF_W(11) KB_PSF_W(13)
         KB_PSF_W(15) KB_PSF_W(17) KB_PSF_W(19) KB_PSF_W(21) KB_PSF_W(23) KB_PSF_W(25)

@@ -678,3 +678,28 @@ def test_batch_of_block_and_dense_jobs_equals_solo(torch_dev):
     for jb, solo in zip(jobs, solos):
         for a, b in zip(parity.to_numpy(jb["out"]), parity.to_numpy(solo)):
             assert a.tobytes() == b.tobytes()
+
+
+@pytest.mark.parametrize("psf_shape", [(1, 1), (3, 5), (11, 11), (21, 7), (25, 25)])
+def test_planes_do_not_depend_on_the_tile_height(torch_dev, psf_shape):
+    """A stack of enough tiles for two rows a thread gives every image bit for
+    bit what it gives alone (one row a thread), variances and pixels whose
+    quotients need scaling, infinities and NaN included."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    rng = np.random.default_rng(91)
+    n, h, w = 600, 97, 387    # 16800 tiles of 64 x 32
+    img = rng.standard_normal((n, h, w)).astype(np.float32)
+    var = rng.uniform(0.5, 2.0, (n, h, w)).astype(np.float32)
+    for value, a in ((1e-38, img), (0.0, img), (-3e18, img), (np.inf, img), (1e-37, var),
+                     (1e19, var), (np.nan, var), (0.0, var)):
+        a[rng.random(a.shape) < 2e-4] = value
+    mask = (rng.random((n, h, w)) < 0.02).astype(np.uint8)
+    psf = rng.uniform(0.0, 1.0, psf_shape).astype(np.float32)
+    _say(f"case tile height psf={psf_shape}")
+    dev = torch.device("cuda:0")
+    d = [torch.from_numpy(a).to(dev) for a in (img, var, mask)]
+    got = lib.make_psi_phi(*d, psf).cpu().numpy()
+    for i in range(0, n, 37):
+        one = lib.make_psi_phi(*(a[i:i + 1].contiguous() for a in d), psf).cpu().numpy()
+        assert one.tobytes() == got[i:i + 1].tobytes()
