@@ -279,6 +279,27 @@ __device__ __forceinline__ void net_merge(uint64_t (&r)[N], float (&ra)[N]) {
     net_place<KM>(r, ra, std::make_index_sequence<KM>());
 }
 
+// Sorts slots [LO, LO + N) descending where they fall and then rise (bitonic,
+// any N: the power of two goes last).
+template <int LO, int N, int KR>
+__device__ __forceinline__ void sort_valley(uint64_t (&key)[KR], float (&al)[KR]) {
+    if constexpr (N > 1) {
+        constexpr int M = N > 32 ? 32 : N > 16 ? 16 : N > 8 ? 8 : N > 4 ? 4 : N > 2 ? 2 : 1;
+#pragma unroll
+        for (int i = LO; i < LO + N - M; ++i) {
+            const uint64_t a = key[i], b = key[i + M];
+            const float fa = al[i], fb = al[i + M];
+            const bool c = b > a;
+            key[i] = c ? b : a;
+            key[i + M] = c ? a : b;
+            al[i] = c ? fb : fa;
+            al[i + M] = c ? fa : fb;
+        }
+        sort_valley<LO, N - M>(key, al);
+        sort_valley<LO + N - M, M>(key, al);
+    }
+}
+
 // Scores of one trajectory (Sec. 2.1.5): nu = Psi / sqrt(Phi) and
 // alpha = Psi / Phi; Phi = 0 (no valid observation) gives nu = -inf and
 // alpha = 0.  Every kernel scores with these functions, so equal sums give
@@ -492,6 +513,15 @@ constexpr int search_lds_words() {
     return search_queue_words<KM, PB>() + kVisitWords;
 }
 
+__device__ inline int wave_lane() { return (int)threadIdx.x & 63; }
+// Orders one wave's LDS accesses (a workgroup may hold waves that are
+// elsewhere): the LDS serves a wave in order, so this only binds the compiler.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sums of one pixel along one trajectory.
 template <int FMT>
 struct PixelSums {
@@ -558,7 +588,7 @@ struct ListCursor {
         : list(l), n(count), q(from) {
         load();
     }
-    __device__ inline void load() { held = list[min((q & ~63) + (int)threadIdx.x, n - 1)]; }
+    __device__ inline void load() { held = list[min((q & ~63) + wave_lane(), n - 1)]; }
     __device__ inline uint32_t entry() const {
         return (uint32_t)__builtin_amdgcn_readlane((int)held, q & 63);
     }
@@ -702,18 +732,19 @@ __device__ __forceinline__ int visit_serial(const Tile<FMT> &t, const float2 *in
 
 #define KB_BATCH_LIST(X) X(2) X(4) X(6) X(8) X(10) X(12) X(14) X(16)
 
-// Every velocity of one tile (start row `row`, start columns seg*64 ..
-// seg*64+63): calls finish(j, P, F, n_obs) with the velocity's original index
-// j and the sums of this lane's pixel, and drain() where full().  All scalar
-// arguments are wave-uniform.  words: kVisitWords of LDS; MAXNV: loads of a
-// batch, at most.
+// The velocities of one tile (start row `row`, start columns seg*64 ..
+// seg*64+63) that wave `part` of `parts` takes, every parts-th chunk of
+// `chunk` (at most kChunk) velocities: calls finish(j, P, F, n_obs) with the
+// velocity's original index j and the sums of this lane's pixel, and drain()
+// where full().  All scalar arguments are wave-uniform.  words: kVisitWords of
+// LDS; MAXNV: loads of a batch, at most.
 template <int FMT, int MAXNV, class Finish, class Full, class Drain>
 __device__ __forceinline__ void visit_velocities(
     uint32_t *words, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
-    const int32_t *__restrict__ vel_index, int n_vel, int row, int seg, Finish &&finish,
-    Full &&full, Drain &&drain) {
-    const int lane = (int)threadIdx.x;
+    const int32_t *__restrict__ vel_index, int n_vel, int row, int seg, int part, int parts,
+    int chunk, Finish &&finish, Full &&full, Drain &&drain) {
+    const int lane = wave_lane();
     Tile<FMT> t;
     t.row_bytes = (uint32_t)w * Tile<FMT>::kPix;
     t.row0 = reinterpret_cast<uint64_t>(planes) + (uint64_t)row * t.row_bytes;
@@ -731,9 +762,12 @@ __device__ __forceinline__ void visit_velocities(
     t.scale = scale;
     t.x = x_first + lane;
     if (FMT != KB_F32 && n_img > kMaxScaleImages) {
-        for (int q = 0; q < n_vel;) {
-            q = visit_serial<FMT>(t, inv_scale, n_vel, q, finish, full);
-            if (full()) drain();
+        for (int v0 = part * chunk; v0 < n_vel; v0 += parts * chunk) {
+            const int end = min(v0 + chunk, n_vel);
+            for (int q = v0; q < end;) {
+                q = visit_serial<FMT>(t, inv_scale, end, q, finish, full);
+                if (full()) drain();
+            }
         }
         return;
     }
@@ -741,7 +775,7 @@ __device__ __forceinline__ void visit_velocities(
         // Image 1 first (0 past the last image: a gather there reads 0).
         const float *isc = reinterpret_cast<const float *>(inv_scale + 1);
         for (int q = lane; q < kScaleWords; q += 64) scale[q] = q < 2 * n_img - 2 ? isc[q] : 0.f;
-        __syncthreads();
+        wave_sync();
     }
     // Image 0 is the start image: its displacement is (0, 0) for every
     // velocity (tau_0 = 0), so its pair is loaded once per tile and every
@@ -753,8 +787,8 @@ __device__ __forceinline__ void visit_velocities(
     }
     const int ni = n_img - 1;
     constexpr int kMulti = MAXNV / 2;    // classes: 0, NV / 2, kMulti + NV / 2 of several parts
-    for (int v0 = 0; v0 < n_vel; v0 += kChunk) {
-        const int nc = min(kChunk, n_vel - v0);
+    for (int v0 = part * chunk; v0 < n_vel; v0 += parts * chunk) {
+        const int nc = min(chunk, n_vel - v0);
         uint32_t present = 0;   // classes of the chunk's velocities
         for (int k0 = 0; k0 < nc; k0 += 64) {
             const int k = k0 + lane;
@@ -798,7 +832,7 @@ __device__ __forceinline__ void visit_velocities(
                         (uint32_t)k | ((uint32_t)t.seen[k] << 16);
                 n += __builtin_popcountll(b);
             }
-            __syncthreads();
+            wave_sync();
             for (int q = 0; q < n;) {
                 if (c0 == 0) {
                     do {
@@ -818,25 +852,28 @@ __device__ __forceinline__ void visit_velocities(
 #undef KB_CASE
                 if (full()) drain();
             }
-            __syncthreads();
+            wave_sync();
         }
     }
 }
 
-// The search of one tile (start row `row`, start columns seg*64 .. seg*64+63).
-// All scalar arguments are wave-uniform.
+// The search of one tile (start row `row`, start columns seg*64 .. seg*64+63)
+// by a workgroup of `parts` waves (a power of two), of which this is wave
+// `part`.  lds: search_lds_words for each wave (and parts / 2 lists, for
+// several).  All scalar arguments are wave-uniform.
 template <int KM, int PB, int FMT>
 __device__ __forceinline__ void search_tile(
-    uint32_t *lds, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
+    uint32_t *group_lds, int part, int parts, int chunk, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, int row, int seg,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs) {
+    uint32_t *lds = group_lds + part * search_lds_words<KM, PB>();
     uint32_t *q_hi = lds;
     uint32_t *q_lo = lds + PB * 64;
     float *q_al = reinterpret_cast<float *>(lds + 2 * PB * 64);
 
-    const int lane = (int)threadIdx.x;
+    const int lane = wave_lane();
 
     // The list (slots 0..KM-1, descending); with the network merge, slots
     // KM..KM+15 receive the queued batch during a merge.
@@ -922,17 +959,50 @@ __device__ __forceinline__ void search_tile(
     // with fewer too: 16 / 12 loads 4.74 / 4.90 and 5.16 / 5.23 ms (15 x 1024^2).
     constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 12 : 16;
     visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
-                                  w, disp, disp_stride, vel_index, n_vel, row, seg, finish, full,
+                                  w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts, chunk, finish, full,
                                   merge_queue);
     do merge_queue();
     while (__any(nq > 0));
+
+    // Several waves: the upper half hands its lists to the lower half until
+    // one is left.  Of two descending lists the larger of slot s and slot
+    // KM - 1 - s are the best KM, falling and then rising.
+    if (parts > 1) {
+        for (int half = parts >> 1; half > 0; half >>= 1) {
+            __syncthreads();   // the LDS is free of queues and of earlier lists
+            uint32_t *slot = group_lds + (part < half ? part : part - half) * (3 * KM * 64) + lane;
+            if (part >= half && part < 2 * half) {
+#pragma unroll
+                for (int s = 0; s < KM; ++s) {
+                    slot[(3 * s) * 64] = (uint32_t)(key[s] >> 32);
+                    slot[(3 * s + 1) * 64] = (uint32_t)key[s];
+                    slot[(3 * s + 2) * 64] = __float_as_uint(al[s]);
+                }
+            }
+            __syncthreads();
+            if (part < half) {
+#pragma unroll
+                for (int s = 0; s < KM; ++s) {
+                    const int o = KM - 1 - s;
+                    const uint64_t k =
+                        ((uint64_t)slot[(3 * o) * 64] << 32) | slot[(3 * o + 1) * 64];
+                    const float a = __uint_as_float(slot[(3 * o + 2) * 64]);
+                    const bool c = k > key[s];
+                    key[s] = c ? k : key[s];
+                    al[s] = c ? a : al[s];
+                }
+                sort_valley<0, KM>(key, al);
+            }
+        }
+        if (part != 0) return;
+    }
 
     // Write the rank-ordered list: stage each field through LDS so that the
     // wave's stores cover the contiguous [pixels][k_cand] run of its pixels
     // (one pixel's k_cand <= 64 entries per store instruction).
     const int npx = (w - seg * 64) < 64 ? (w - seg * 64) : 64;
     const size_t base = ((size_t)row * (size_t)w + (size_t)seg * 64) * (size_t)k_cand;
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int field = 0; field < 4; ++field) {
 #pragma unroll
@@ -944,7 +1014,7 @@ __device__ __forceinline__ void search_tile(
             else v = (uint32_t)key_nobs(key[s]);
             lds[lane * KM + s] = v;
         }
-        __syncthreads();
+        wave_sync();
         if (lane < k_cand) {
             for (int p = 0; p < npx; ++p) {
                 const uint32_t v = lds[p * KM + lane];
@@ -955,7 +1025,7 @@ __device__ __forceinline__ void search_tile(
                 else cand_nobs[o] = (int16_t)v;
             }
         }
-        __syncthreads();
+        wave_sync();
     }
 }
 
@@ -969,8 +1039,33 @@ __global__ __launch_bounds__(64, 2) void search_kernel(
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
-    search_tile<KM, PB, FMT>(lds, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index,
+    search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index,
                              n_vel, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
+}
+
+// The single-stack search of frames with too few tiles to fill the GPU: the
+// workgroup's waves share a tile's velocities.
+constexpr size_t kLdsBytes = 160 * 1024;   // of a CU
+template <int KM, int PB>
+constexpr size_t search_split_lds_bytes(int parts) {
+    const size_t a = (size_t)parts * search_lds_words<KM, PB>() * 4;
+    const size_t b = (size_t)(parts / 2) * 3 * KM * 64 * 4;
+    return a > b ? a : b;
+}
+template <int KM, int PB, int FMT>
+__global__ __launch_bounds__(512, 2) void search_split_kernel(
+    const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
+    int w, const GatherEntry *__restrict__ disp, int disp_stride,
+    const int32_t *__restrict__ vel_index, int n_vel, int k_cand, TileMap tiles, int chunk,
+    float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
+    int16_t *__restrict__ cand_nobs) {
+    extern __shared__ __align__(16) uint32_t split_lds[];
+    int row, seg;
+    tiles.map(blockIdx.x, row, seg);
+    const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    search_tile<KM, PB, FMT>(split_lds, part, (int)blockDim.x >> 6, chunk, planes, inv_scale,
+                             n_img, h, w, disp, disp_stride, vel_index, n_vel, k_cand, row, seg,
+                             cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
 
 // The single-stack search in the persistent order (large frames).
@@ -989,7 +1084,7 @@ __global__ __launch_bounds__(64, 2) void search_persistent_kernel(
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
         if (pm.map(gen, (int)blockIdx.x, row, seg)) {
-            search_tile<KM, PB, FMT>(lds, planes, inv_scale, n_img, h, w, disp, disp_stride,
+            search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride,
                                      vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
                                      cand_vel, cand_nobs);
         }
@@ -1068,7 +1163,7 @@ __global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__r
         }
         if (ok)
             search_tile<KM, PB, FMT>(
-                lds, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp, jb.disp_stride,
+                lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp, jb.disp_stride,
                 jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
                 jb.cand_vel, jb.cand_nobs);
         if (gen >= paced) continue;

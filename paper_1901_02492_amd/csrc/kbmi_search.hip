@@ -81,6 +81,29 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
         }
     }
     const TileMap tm = tile_map(v.w, v.h);
+    // Frames whose tiles leave waves idle: up to 8 waves share a tile's
+    // velocities, as many as the device still holds at once (2048 waves), in
+    // two chunks each so that waves with short and long chunks even out.  A
+    // tile's wave otherwise waits for its own gathers only: 64 tiles, 121
+    // velocities, K = 5: 82 us with 1 wave, 61 with 2, 49 with 4, 42 with 8; 300
+    // tiles, 600 velocities, K = 50: 335, 239, 167, 176; 800 tiles, 3600 velocities,
+    // 16-bit: 2070, 1430, 1640, 1770; 1255 tiles, 400 velocities: 279, 314, 297,
+    // 385 (the merges of K = 50 lists and the shorter class runs cost more
+    // than the idle waves).
+    const int resident = resident_workgroups<search_kernel<KM, PB, KBMI_FMT>>();
+    int parts = 1;
+    while (parts < 8 && (int64_t)tm.nblocks * parts * 2 <= resident && v.n_vel >= 16 * parts &&
+           search_split_lds_bytes<KM, PB>(2 * parts) <= kLdsBytes)
+        parts *= 2;
+    if (parts > 1) {
+        const int chunk = std::min(kChunk, std::max(8, (v.n_vel + 2 * parts - 1) / (2 * parts)));
+        hipLaunchKernelGGL((search_split_kernel<KM, PB, KBMI_FMT>), dim3(tm.nblocks),
+                           dim3(64 * parts), (search_split_lds_bytes<KM, PB>(parts)), s, v.planes,
+                           v.inv_scale, v.n_img, v.h, v.w, v.disp, v.disp_stride, v.vel_index,
+                           v.n_vel, v.k_cand, tm, chunk, v.cand_nu, v.cand_alpha, v.cand_vel,
+                           v.cand_nobs);
+        return launch_status("search_split_kernel");
+    }
     hipLaunchKernelGGL((search_kernel<KM, PB, KBMI_FMT>), dim3(tm.nblocks), dim3(64), 0, s,
                        v.planes, v.inv_scale, v.n_img, v.h, v.w, v.disp, v.disp_stride,
                        v.vel_index, v.n_vel, v.k_cand, tm, v.cand_nu, v.cand_alpha, v.cand_vel,

@@ -67,7 +67,8 @@ __device__ __forceinline__ void threshold_tile(
         }
     };
     visit_velocities<KB_F32, TH_NV>(lds, planes, nullptr, n_img, h, w, disp, disp_stride,
-                                    vel_index, n_vel, row, seg, finish, []() { return false; },
+                                    vel_index, n_vel, row, seg, 0, 1, kChunk, finish,
+                                    []() { return false; },
                                     []() {});
 }
 

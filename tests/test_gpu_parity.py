@@ -703,3 +703,25 @@ def test_planes_do_not_depend_on_the_tile_height(torch_dev, psf_shape):
     for i in range(0, n, 37):
         one = lib.make_psi_phi(*(a[i:i + 1].contiguous() for a in d), psf).cpu().numpy()
         assert one.tobytes() == got[i:i + 1].tobytes()
+
+
+@pytest.mark.parametrize("lp", [None, "bf16"])
+@pytest.mark.parametrize("k", [1, 5, 16, 27, 50, 64])
+@pytest.mark.parametrize("h", [20, 290, 700])
+def test_tile_shared_by_several_waves_equals_one(torch_dev, h, k, lp):
+    """Frames of 20, 290 and 700 tiles, whose tiles 8, 4 and 2 waves share, bit
+    for bit as one wave a tile finds them (a batch does not share tiles)."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    s = synth.random_stack(95, n=7, h=h, w=59, n_vel=150, k=k, psf_size=5, vmax=70.0)
+    _say(f"case shared tile h={h} k={k} lp={lp}")
+    d = (torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask))
+    src, sc = (lib.make_psi_phi(*d, s.psf), None) if lp is None else \
+        lib.make_psi_phi(*d, s.psf, lp=lp)[1:]
+    solo = lib.search(src, s.t, s.vel, k, lp_scale=sc)
+    out = lib.alloc_candidates(h, 59, k, dev)
+    lib.search_batch([dict(planes=src, t=s.t, vel=s.vel, out=out, lp_scale=sc)], k)
+    torch.cuda.synchronize()
+    for a, b in zip(parity.to_numpy(solo), parity.to_numpy(out)):
+        assert a.tobytes() == b.tobytes()
