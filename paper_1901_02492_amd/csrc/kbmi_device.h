@@ -34,13 +34,6 @@
 #ifndef KBMI_PERSIST_PER_CU
 #define KBMI_PERSIST_PER_CU 8   // persistent grid: at most this many one-wave workgroups per CU
 #endif
-// Queued candidates per lane before a merge.  Eight waves' queues and lists
-// just fit a CU's LDS; a merge takes 16, so a queue of 22 is fuller when one
-// of its wave's lanes runs full (16 -> 22: 12 x 251 x 301, 400 velocities 0.291 ->
-// 0.281 ms; 25 x 1024 x 2048 f16, 4000 velocities 75.2 -> 74.3 ms).
-#ifndef KBMI_QUEUE
-#define KBMI_QUEUE 22
-#endif
 // List lengths compiled for the search (each slot costs registers and
 // compare-and-swap work on every insertion); a search keeps k_cand
 // candidates in the shortest compiled list of at least k_cand slots, which
@@ -98,6 +91,23 @@ struct BatchShape {
     int grid, generations, paced;
     uint32_t *sync;
 };
+
+// Waves of a search kernel per SIMD.  16-bit planes take as many as short lists
+// leave registers for: 12 x 700^2, 640 velocities, K = 5 1.469 ms with 2, 1.222 with 3,
+// 0.990 with 4; 19 x 786 x 1693, 640 velocities, K = 20 6.38 with 2, 5.30 with 3.
+// Float32 planes, whose gathers keep the memory path busy with two, lose as
+// much by the shorter queue: 20 x 500 x 900, K = 10 2.14 ms with 2, 2.19 with 3, 2.43 with 4.
+constexpr int search_waves(int km, int fmt) {
+    return fmt == KB_F32 || km > 20 ? 2 : km <= 12 ? 4 : 3;
+}
+// Queued candidates per lane before a merge: as many as that many waves' queues
+// and lists leave room for in a CU's LDS.  A merge takes 16; with a queue of 22 more of
+// them are filled when one of the wave's lanes runs full (K = 50, 16 -> 22:
+// 12 x 251 x 301, 400 velocities 0.291 -> 0.281 ms; 25 x 1024 x 2048 f16, 4000
+// velocities 75.2 -> 74.3 ms).
+constexpr int search_queue(int km, int fmt) {
+    return search_waves(km, fmt) == 4 ? 9 : search_waves(km, fmt) == 3 ? 14 : 22;
+}
 
 kb_status launch_status(const char *what);
 
@@ -490,9 +500,9 @@ __device__ inline float lp_value(uint32_t bits16, int fmt) {
 // when a queue is full, and its gathers in flight are issued again after the
 // merge.
 //
-// The kernel is bounded to two waves per SIMD (the list takes the registers):
-// memory-level parallelism comes from the waves, each with two batches' gathers
-// in flight.
+// The list's registers bound the kernel to two to four waves per SIMD
+// (search_waves): memory-level parallelism comes from the waves, each with two
+// batches' gathers in flight.
 // ---------------------------------------------------------------------------
 constexpr int kChunk = 256;           // velocities classified at once
 constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales fit the LDS
@@ -878,7 +888,7 @@ __device__ __forceinline__ void search_tile(
     // The list (slots 0..KM-1, descending); with the network merge, slots
     // KM..KM+15 receive the queued batch during a merge.
     constexpr int kBatch = 16;   // queued candidates a network merge takes
-    constexpr bool kNet = KM >= 16 && PB >= kBatch;
+    constexpr bool kNet = KM >= 16;
     constexpr int KR = kNet ? KM + kBatch : KM;
     uint64_t key[KR];
     float al[KR];
@@ -910,10 +920,12 @@ __device__ __forceinline__ void search_tile(
             // batch moves to the front.
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const uint64_t nk = ((uint64_t)q_hi[b * 64 + lane] << 32) | q_lo[b * 64 + lane];
-                const float na = q_al[b * 64 + lane];
-                key[KM + b] = b < nq ? nk : 0;
-                al[KM + b] = b < nq ? na : 0.f;
+                const int at = (b < PB ? b : 0) * 64 + lane;
+                const bool queued = b < PB && b < nq;
+                const uint64_t nk = ((uint64_t)q_hi[at] << 32) | q_lo[at];
+                const float na = q_al[at];
+                key[KM + b] = queued ? nk : 0;
+                al[KM + b] = queued ? na : 0.f;
             }
             net_merge<KM>(key, al);
 #pragma unroll
@@ -1030,7 +1042,7 @@ __device__ __forceinline__ void search_tile(
 }
 
 template <int KM, int PB, int FMT>
-__global__ __launch_bounds__(64, 2) void search_kernel(
+__global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, int k_cand, TileMap tiles, float *__restrict__ cand_nu,
@@ -1070,7 +1082,7 @@ __global__ __launch_bounds__(512, 2) void search_split_kernel(
 
 // The single-stack search in the persistent order (large frames).
 template <int KM, int PB, int FMT>
-__global__ __launch_bounds__(64, 2) void search_persistent_kernel(
+__global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, PersistMap pm,
@@ -1123,7 +1135,7 @@ __global__ void zero_words_kernel(uint32_t *p, int n) {
 // batched with.
 // ---------------------------------------------------------------------------
 template <int KM, int PB, int FMT>
-__global__ __launch_bounds__(64, 2) void search_batch_kernel(const BatchJob *__restrict__ jobs_,
+__global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel(const BatchJob *__restrict__ jobs_,
                                                              int n_jobs, int generations,
                                                              int paced, int spin, int k_cand,
                                                              uint32_t *sync) {

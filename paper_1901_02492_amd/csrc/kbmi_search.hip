@@ -48,7 +48,7 @@ int resident_workgroups() {
 
 template <int KM>
 kb_status launch_one(const StackView &v, hipStream_t s) {
-    constexpr int PB = KBMI_QUEUE;
+    constexpr int PB = search_queue(KM, KBMI_FMT);
     // The persistent order pays where gathers dominate (float32 planes); the
     // 16-bit search keeps the super-strip order, which measured faster (60 ms
     // against 76 ms on a 15 x 4096^2 stack at 600 velocities, K = 50).
@@ -114,7 +114,7 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
 template <int KM>
 kb_status launch_batch_km(const BatchJob *jobs, const BatchShape &b, int *resident,
                           hipStream_t s) {
-    constexpr int PB = KBMI_QUEUE;
+    constexpr int PB = search_queue(KM, KBMI_FMT);
     auto kernel = search_batch_kernel<KM, PB, KBMI_FMT>;
     if (!jobs) {
         const int g = resident_workgroups<search_batch_kernel<KM, PB, KBMI_FMT>>();
