@@ -549,6 +549,41 @@ def test_rescore_of_any_image_count_and_far_velocities(torch_dev, n):
         assert np.ascontiguousarray(a).tobytes() == np.ascontiguousarray(b).tobytes()
 
 
+@pytest.mark.parametrize("kc", [2, 9, 50, 64])
+def test_rescore_ranks_repeated_and_unknown_velocities(torch_dev, kc):
+    """Lists that name velocities twice or outside the grid, beside lists that
+    do not: the rank order is nu descending, velocity ascending, then list
+    order, with unknown ones last in list order."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    n, h, w, nv = 5, 17, 67, 64
+    s = synth.random_stack(88, n=n, h=h, w=w, n_vel=nv, k=nv, psf_size=5, vmax=60)
+    _say(f"case repeated rescore kc={kc}")
+    planes = lib.make_psi_phi(*(torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask)),
+                              s.psf)
+    full = [np.ascontiguousarray(a) for a in
+            parity.to_numpy(lib.topk(lib.search(planes, s.t, s.vel, nv), nv, n))]
+    rng = np.random.default_rng(kc)
+    cv = np.argsort(rng.random((h, w, nv)), axis=-1)[..., :kc].astype(np.int32)
+    twice = rng.random((h, w)) < 0.5
+    cv[twice] = rng.integers(-2, nv + 2, (int(twice.sum()), kc))
+    at = np.argsort(full[2], axis=-1)          # place of each velocity in the full list
+    known = (cv >= 0) & (cv < nv)
+    take = [np.take_along_axis(f, np.take_along_axis(at, np.where(known, cv, 0), -1), -1)
+            for f in full]
+    nu = np.where(known, take[0], -np.inf).astype(np.float32)
+    al = np.where(known, take[1], 0).astype(np.float32)
+    no = np.where(known, take[3], 0).astype(np.int16)
+    order = np.lexsort((np.where(known, cv, 0), -nu.astype(np.float64), ~known), axis=-1)
+    cand = lib.alloc_candidates(h, w, kc, dev)
+    cand[2].copy_(torch.from_numpy(cv))
+    got = parity.to_numpy(lib.topk(cand, kc, n, rescore=(planes, s.t, s.vel, None)))
+    torch.cuda.synchronize()
+    for g, want in zip(got, (nu, al, cv, no)):
+        np.testing.assert_array_equal(g, np.take_along_axis(want, order, -1))
+
+
 LP_BAND = {"f16": 1e-2, "bf16": 8e-2}   # nu band for near-ties after 16-bit pre-selection
 
 
