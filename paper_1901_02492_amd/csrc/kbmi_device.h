@@ -873,7 +873,8 @@ __device__ __forceinline__ void visit_velocities(
 // several).  All scalar arguments are wave-uniform.
 template <int KM, int PB, int FMT>
 __device__ __forceinline__ void search_tile(
-    uint32_t *group_lds, int part, int parts, int chunk, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
+    uint32_t *group_lds, int part, int parts, int chunk, const void *__restrict__ planes,
+    const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, int row, int seg,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
@@ -971,8 +972,8 @@ __device__ __forceinline__ void search_tile(
     // with fewer too: 16 / 12 loads 4.74 / 4.90 and 5.16 / 5.23 ms (15 x 1024^2).
     constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 12 : 16;
     visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
-                                  w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts, chunk, finish, full,
-                                  merge_queue);
+                                  w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts, chunk,
+                                  finish, full, merge_queue);
     do merge_queue();
     while (__any(nq > 0));
 
@@ -1044,15 +1045,16 @@ __device__ __forceinline__ void search_tile(
 template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
-    int w, const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
+    int w, const GatherEntry *__restrict__ disp, int disp_stride,
+    const int32_t *__restrict__ vel_index,
     int n_vel, int k_cand, TileMap tiles, float *__restrict__ cand_nu,
     float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs) {
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
-    search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index,
-                             n_vel, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
+    search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride,
+                             vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
 
 // The single-stack search of frames with too few tiles to fill the GPU: the
@@ -1096,8 +1098,8 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_k
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
         if (pm.map(gen, (int)blockIdx.x, row, seg)) {
-            search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride,
-                                     vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
+            search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
+                                     disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
                                      cand_vel, cand_nobs);
         }
         // Generation boundary: wait (a bounded time) until every workgroup of
@@ -1135,10 +1137,9 @@ __global__ void zero_words_kernel(uint32_t *p, int n) {
 // batched with.
 // ---------------------------------------------------------------------------
 template <int KM, int PB, int FMT>
-__global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel(const BatchJob *__restrict__ jobs_,
-                                                             int n_jobs, int generations,
-                                                             int paced, int spin, int k_cand,
-                                                             uint32_t *sync) {
+__global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel(
+    const BatchJob *__restrict__ jobs_, int n_jobs, int generations, int paced, int spin,
+    int k_cand, uint32_t *sync) {
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     // The descriptors do not change during the launch: read through the
     // constant address space, their fields stay in scalar registers.
@@ -1175,8 +1176,8 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel
         }
         if (ok)
             search_tile<KM, PB, FMT>(
-                lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp, jb.disp_stride,
-                jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
+                lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp,
+                jb.disp_stride, jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
                 jb.cand_vel, jb.cand_nobs);
         if (gen >= paced) continue;
         // Generation boundary (as in the single-stack persistent search).

@@ -379,7 +379,8 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
     int k, int pt, int h, int w, int row0, int n_rows, int n_img,
     const float2 *__restrict__ planes, const double *__restrict__ tau,
     const double2 *__restrict__ vels, int n_vel, double c2, double q,
-    float q_span, const int32_t *__restrict__ cand_vel, float *__restrict__ nu, float *__restrict__ alpha,
+    float q_span, const int32_t *__restrict__ cand_vel, float *__restrict__ nu,
+    float *__restrict__ alpha,
     int16_t *__restrict__ nobs, uint64_t *__restrict__ rejected) {
     extern __shared__ __align__(16) unsigned char lc_lds[];
     const int np_max = pt * k;
@@ -487,13 +488,13 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
 template <int NB>
 kb_status launch_lightcurve(int64_t ncand, int k, int h, int w, int n_img, const float2 *planes,
                             const double *tau, const double2 *vels, int n_vel, double c2,
-                            double q, float q_span, const int32_t *cv, float *nu, float *al, int16_t *no,
-                            uint64_t *rej, hipStream_t s) {
+                            double q, float q_span, const int32_t *cv, float *nu, float *al,
+                            int16_t *no, uint64_t *rej, hipStream_t s) {
     if (k > LC_PAIRS) {
         const int64_t blocks = (ncand + LC_THREADS - 1) / LC_THREADS;
         hipLaunchKernelGGL(lightcurve_kernel<NB>, dim3((unsigned)blocks), dim3(LC_THREADS), 0, s,
-                           ncand, k, h, w, n_img, planes, tau, vels, n_vel, c2, q, q_span, cv, nu, al,
-                           no, rej);
+                           ncand, k, h, w, n_img, planes, tau, vels, n_vel, c2, q, q_span, cv, nu,
+                           al, no, rej);
         return launch_status("lightcurve_kernel");
     }
     // Eight workgroups per row for each group of eight tile columns; rows in
@@ -506,8 +507,8 @@ kb_status launch_lightcurve(int64_t ncand, int k, int h, int w, int n_img, const
         const int n_rows = (int)std::min<int64_t>(max_rows, h - r0);
         hipLaunchKernelGGL(lightcurve_grouped_kernel<NB>, dim3((unsigned)(per_row * n_rows)),
                            dim3(LC_THREADS), lightcurve_lds_bytes(pt * k), s, k, pt, h, w,
-                           (int)r0, n_rows, n_img, planes, tau, vels, n_vel, c2, q, q_span, cv, nu, al,
-                           no, rej);
+                           (int)r0, n_rows, n_img, planes, tau, vels, n_vel, c2, q, q_span, cv, nu,
+                           al, no, rej);
         const kb_status st = launch_status("lightcurve_grouped_kernel");
         if (st != KB_OK) return st;
     }
