@@ -967,10 +967,11 @@ __device__ __forceinline__ void search_tile(
     auto full = [&]() { return __any(nq >= PB - 1) != 0; };
 
     // Loads of a batch: two batches lie beside the list.  16-bit planes, 25
-    // images, K = 50: 16 / 12 / 8 loads 73.8 / 77.0 / 87.9 ms; K = 52 spills with
-    // 16: 1.283 ms against 1.174 with 12 (9 x 613 x 1187); K = 60 and 64 spill
+    // images, K = 50: 16 / 12 / 8 loads 73.8 / 77.0 / 87.9 ms.  K = 52 spills with 16,
+    // and 12 split the usual 14 images: 16 / 14 / 12 loads 24.4 / 23.0 / 29.1 ms (15 x
+    // 2048^2, 900 velocities), 1.292 / 1.212 / 1.182 (9 x 613 x 1187).  K = 60 and 64 spill
     // with fewer too: 16 / 12 loads 4.74 / 4.90 and 5.16 / 5.23 ms (15 x 1024^2).
-    constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 12 : 16;
+    constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 14 : 16;
     visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
                                   w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts, chunk,
                                   finish, full, merge_queue);
