@@ -426,6 +426,7 @@ struct PersistMap {
     int nbc, nbr;      // blocks per row of blocks, rows of blocks
     int generations;   // block_generations(nbc, nbr)
     int spin;          // bound of a wave's wait at a generation boundary (0: no wait)
+    int long_walk;     // 1: also wait after every kPaceVelocities velocities
     __device__ inline bool map(int gen, int w, int &row, int &seg) const {
         const int xcd = w & 7, k = w >> 3;
         const int sc = min(gen / nbr, nbc >> 3);
@@ -505,6 +506,18 @@ __device__ inline float lp_value(uint32_t bits16, int fmt) {
 // batches' gathers in flight.
 // ---------------------------------------------------------------------------
 constexpr int kChunk = 256;           // velocities classified at once
+// Velocities between two paces inside a tile of a long walk.  Tiles that see
+// fewer images run ahead of the others of their XCD's block, and with more
+// images than 17 an XCD's L2 holds hardly more than one velocity's windows
+// (24 displaced images: 3.1 MB of 4), so over thousands of velocities the block
+// falls apart: 25 x 4096^2, 4000 velocities, float32 1521 ms with the generation's
+// pace alone, 714 with one every 1024 velocities too (903 without classes, in
+// step by themselves); 25 x 2048 x 4096, 3000 velocities 284 -> 266.  Fewer images
+// lose by the waiting (13 x 1024^2, 32000 velocities, every 512: 186 -> 228).
+// 16-bit planes walk in the paced order then: 25 x 1024 x 2048, 4000 velocities
+// 73.8 -> 65.9 ms, 25 x 4096^2 757 -> 608, 25 x 2048 x 4096, 3000 velocities 272 -> 228.
+constexpr int kPaceVelocities = 1024;
+static_assert(kPaceVelocities % kChunk == 0, "a pace stands between two chunks");
 constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales fit the LDS
 constexpr int kScaleWords = 2 * kMaxScaleImages + 2 * 16;
 // LDS words of visit_velocities: a chunk's list and classes, then the inverse
@@ -746,14 +759,15 @@ __device__ __forceinline__ int visit_serial(const Tile<FMT> &t, const float2 *in
 // seg*64+63) that wave `part` of `parts` takes, every parts-th chunk of
 // `chunk` (at most kChunk) velocities: calls finish(j, P, F, n_obs) with the
 // velocity's original index j and the sums of this lane's pixel, and drain()
-// where full().  All scalar arguments are wave-uniform.  words: kVisitWords of
-// LDS; MAXNV: loads of a batch, at most.
-template <int FMT, int MAXNV, class Finish, class Full, class Drain>
+// where full(), and pace() after every kPaceVelocities velocities.  All scalar
+// arguments are wave-uniform.  words: kVisitWords of LDS; MAXNV: loads of a
+// batch, at most.
+template <int FMT, int MAXNV, class Finish, class Full, class Drain, class Pace>
 __device__ __forceinline__ void visit_velocities(
     uint32_t *words, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int row, int seg, int part, int parts,
-    int chunk, Finish &&finish, Full &&full, Drain &&drain) {
+    int chunk, Finish &&finish, Full &&full, Drain &&drain, Pace &&pace) {
     const int lane = wave_lane();
     Tile<FMT> t;
     t.row_bytes = (uint32_t)w * Tile<FMT>::kPix;
@@ -798,6 +812,7 @@ __device__ __forceinline__ void visit_velocities(
     const int ni = n_img - 1;
     constexpr int kMulti = MAXNV / 2;    // classes: 0, NV / 2, kMulti + NV / 2 of several parts
     for (int v0 = part * chunk; v0 < n_vel; v0 += parts * chunk) {
+        if (v0 > 0 && v0 % kPaceVelocities == 0) pace();
         const int nc = min(chunk, n_vel - v0);
         uint32_t present = 0;   // classes of the chunk's velocities
         for (int k0 = 0; k0 < nc; k0 += 64) {
@@ -871,9 +886,9 @@ __device__ __forceinline__ void visit_velocities(
 // by a workgroup of `parts` waves (a power of two), of which this is wave
 // `part`.  lds: search_lds_words for each wave (and parts / 2 lists, for
 // several).  All scalar arguments are wave-uniform.
-template <int KM, int PB, int FMT>
+template <int KM, int PB, int FMT, class Pace>
 __device__ __forceinline__ void search_tile(
-    uint32_t *group_lds, int part, int parts, int chunk, const void *__restrict__ planes,
+    Pace &&pace, uint32_t *group_lds, int part, int parts, int chunk, const void *__restrict__ planes,
     const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, int row, int seg,
@@ -974,7 +989,7 @@ __device__ __forceinline__ void search_tile(
     constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 14 : 16;
     visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
                                   w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts, chunk,
-                                  finish, full, merge_queue);
+                                  finish, full, merge_queue, pace);
     do merge_queue();
     while (__any(nq > 0));
 
@@ -1051,10 +1066,11 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_kernel(
     int n_vel, int k_cand, TileMap tiles, float *__restrict__ cand_nu,
     float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs) {
+    auto pace = []() {};
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
-    search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride,
+    search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride,
                              vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
 
@@ -1074,11 +1090,12 @@ __global__ __launch_bounds__(512, 2) void search_split_kernel(
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, TileMap tiles, int chunk,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs) {
+    auto pace = []() {};
     extern __shared__ __align__(16) uint32_t split_lds[];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
     const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    search_tile<KM, PB, FMT>(split_lds, part, (int)blockDim.x >> 6, chunk, planes, inv_scale,
+    search_tile<KM, PB, FMT>(pace, split_lds, part, (int)blockDim.x >> 6, chunk, planes, inv_scale,
                              n_img, h, w, disp, disp_stride, vel_index, n_vel, k_cand, row, seg,
                              cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
@@ -1096,19 +1113,17 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_k
     const uint32_t per_xcd = gridDim.x >> 3;
     int spin = pm.spin;   // 0 once a wait has timed out (the XCD's workgroups are
                           // not all resident, e.g. beside another launch)
-    for (int gen = 0; gen < pm.generations; ++gen) {
-        int row, seg;
-        if (pm.map(gen, (int)blockIdx.x, row, seg)) {
-            search_tile<KM, PB, FMT>(lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
-                                     disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
-                                     cand_vel, cand_nobs);
-        }
-        // Generation boundary: wait (a bounded time) until every workgroup of
-        // this XCD has finished the generation, so its waves start the next
-        // block together.  The wait only shapes timing; no result depends on it.
+    uint32_t target = 0;
+    // This workgroup is n waits further; then wait (a bounded time) until every
+    // workgroup of this XCD is, so that its waves go on together.  The wait only
+    // shapes timing; no result depends on it.
+    auto arrive = [&](int n) {
         if (threadIdx.x == 0)
-            __hip_atomic_fetch_add(xcd_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t target = (uint32_t)(gen + 1) * per_xcd;
+            __hip_atomic_fetch_add(xcd_count, (uint32_t)n, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        target += (uint32_t)n * per_xcd;
+    };
+    auto wait = [&]() {
         int i = 0;
         for (; i < spin; ++i) {
             if (__hip_atomic_load(xcd_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
@@ -1117,6 +1132,23 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_k
             __builtin_amdgcn_s_sleep(8);
         }
         if (i == spin) spin = 0;
+    };
+    const int paces = pm.long_walk ? (n_vel - 1) / kPaceVelocities : 0;   // inside a tile
+    auto pace = [&]() {
+        if (pm.long_walk) {
+            arrive(1);
+            wait();
+        }
+    };
+    for (int gen = 0; gen < pm.generations; ++gen) {
+        int row, seg;
+        const bool ok = pm.map(gen, (int)blockIdx.x, row, seg);
+        if (ok)
+            search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
+                                     disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu,
+                                     cand_alpha, cand_vel, cand_nobs);
+        arrive(ok ? 1 : 1 + paces);   // generation boundary
+        wait();
     }
 }
 
@@ -1141,6 +1173,7 @@ template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel(
     const BatchJob *__restrict__ jobs_, int n_jobs, int generations, int paced, int spin,
     int k_cand, uint32_t *sync) {
+    auto pace = []() {};
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     // The descriptors do not change during the launch: read through the
     // constant address space, their fields stay in scalar registers.
@@ -1177,7 +1210,7 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel
         }
         if (ok)
             search_tile<KM, PB, FMT>(
-                lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp,
+                pace, lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp,
                 jb.disp_stride, jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
                 jb.cand_vel, jb.cand_nobs);
         if (gen >= paced) continue;

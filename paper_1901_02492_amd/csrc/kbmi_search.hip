@@ -49,10 +49,12 @@ int resident_workgroups() {
 template <int KM>
 kb_status launch_one(const StackView &v, hipStream_t s) {
     constexpr int PB = search_queue(KM, KBMI_FMT);
-    // The persistent order pays where gathers dominate (float32 planes); the
-    // 16-bit search keeps the super-strip order, which measured faster (60 ms
-    // against 76 ms on a 15 x 4096^2 stack at 600 velocities, K = 50).
-    if constexpr (KBMI_FMT == KB_F32) {
+    // The persistent order pays for float32 planes; the 16-bit search keeps the
+    // super-strip order, which measured faster (15 x 2048^2, 600 velocities, K = 50:
+    // 14.1 ms against 17.6), except on long walks (kPaceVelocities).
+    const bool long_walk = v.n_img > 17 && v.n_vel >= 2 * kPaceVelocities &&
+                           (KBMI_FMT == KB_F32 || v.n_img <= kMaxScaleImages);
+    if (KBMI_FMT == KB_F32 || (long_walk && search_waves(KM, KBMI_FMT) == 2)) {
         auto kernel = search_persistent_kernel<KM, PB, KBMI_FMT>;
         const int grid =
             resident_workgroups<search_persistent_kernel<KM, PB, KBMI_FMT>>();
@@ -70,6 +72,7 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
             pm.nbr = (v.h + pm.brows - 1) / pm.brows;
             pm.generations = block_generations(pm.nbc, pm.nbr);
             pm.spin = KBMI_PERSIST_SPIN;
+            pm.long_walk = long_walk;
             hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, v.sync, 8);
             kb_status st = launch_status("zero_words_kernel");
             if (st != KB_OK) return st;

@@ -68,8 +68,7 @@ __device__ __forceinline__ void threshold_tile(
     };
     visit_velocities<KB_F32, TH_NV>(lds, planes, nullptr, n_img, h, w, disp, disp_stride,
                                     vel_index, n_vel, row, seg, 0, 1, kChunk, finish,
-                                    []() { return false; },
-                                    []() {});
+                                    []() { return false; }, []() {}, []() {});
 }
 
 // Strip tile order, one wave per tile.
@@ -465,6 +464,7 @@ kb_status launch_threshold(const float *psi_phi, int64_t n_img, int64_t h, int64
         pm.nbr = ((int)h + pm.brows - 1) / pm.brows;
         pm.generations = block_generations(pm.nbc, pm.nbr);
         pm.spin = KBMI_PERSIST_SPIN;
+        pm.long_walk = 0;
         uint32_t *sync = reinterpret_cast<uint32_t *>(ws + lay.sync);
         hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, sync, 8);
         kb_status st = launch_status("zero_words_kernel");

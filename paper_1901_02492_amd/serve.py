@@ -8,7 +8,7 @@ arrive while others run.  The scheduler
   * prepares each admitted request on the device (inputs, likelihood planes,
     candidate and result buffers) as soon as it is admitted;
   * launches prepared requests in arrival order, packing consecutive ones
-    into ONE batched search (kb_search_batch: one persistent launch over the
+    into ONE batched search (kb_search_batch: one launch over the
     tiles of all those stacks) while the batch's work stays within
     `batch_work` trajectory-image evaluations (a larger request runs alone,
     so small stacks never wait for a large one that shares their launch),

@@ -760,3 +760,25 @@ def test_tile_shared_by_several_waves_equals_one(torch_dev, h, k, lp):
     torch.cuda.synchronize()
     for a, b in zip(parity.to_numpy(solo), parity.to_numpy(out)):
         assert a.tobytes() == b.tobytes()
+
+
+@pytest.mark.parametrize("lp", [None, "f16"])
+def test_long_walk_paced_inside_tiles_equals_batch(torch_dev, lp):
+    """More than 17 images and 2048 velocities on a frame of several
+    generations, ragged on both sides: bit for bit what a batch, which paces no
+    tile inside, finds."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    n, h, w, nv, k = 18, 131, 4099, 2150, 50
+    s = synth.random_stack(96, n=n, h=h, w=w, n_vel=nv, k=k, psf_size=5, vmax=200.0)
+    _say(f"case long walk lp={lp}")
+    d = (torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask))
+    src, sc = (lib.make_psi_phi(*d, s.psf), None) if lp is None else \
+        lib.make_psi_phi(*d, s.psf, lp=lp)[1:]
+    solo = lib.search(src, s.t, s.vel, k, lp_scale=sc)
+    out = lib.alloc_candidates(h, w, k, dev)
+    lib.search_batch([dict(planes=src, t=s.t, vel=s.vel, out=out, lp_scale=sc)], k)
+    torch.cuda.synchronize()
+    for a, b in zip(solo, out):
+        assert torch.equal(a, b)
