@@ -406,13 +406,12 @@ typedef struct kb_job {
 size_t kb_search_batch_workspace_bytes(const kb_job *jobs, int64_t n_jobs);
 
 /*
- * kb_search_batch - kb_search for several stacks in one persistent launch
- * per image-count class (at most three: n_img <= 8, <= 16, > 16; the serving
- * path: small stacks share the GPU instead of each under-filling it).  The
- * launch's grid is what the GPU holds at once; its work items are the jobs'
- * start-pixel tiles, packed tile after tile, except that a job of float32
- * planes large enough for kb_search's paced block order starts at a
- * generation boundary and keeps that order.  All jobs share `dtype` and
+ * kb_search_batch - kb_search for several stacks in one launch, whatever
+ * their image counts (the serving path: small stacks share the GPU instead
+ * of each under-filling it).  Its work items are the jobs' start-pixel tiles,
+ * tile after tile, those of the longest tiles first; a job of float32
+ * planes large enough for kb_search's paced block order comes before them
+ * and keeps that order.  All jobs share `dtype` and
  * `k_cand`.  Each job's candidates are exactly what kb_search would write
  * for it alone (same arithmetic, same order), whatever else is in the batch.
  *   jobs       host array of n_jobs (1 <= n_jobs <= 4096) descriptors; read
