@@ -482,8 +482,9 @@ __device__ inline float lp_value(uint32_t bits16, int fmt) {
 // the table's own displacements, a velocity per lane.  A load per image ->
 // classes and balanced tile orders: 13 x 1024^2, 32000 velocities, K = 50
 // 237 -> 165 ms (15.0 -> 8.9 loads a velocity); 12 x 251 x 301, 400 velocities 0.374 ->
-// 0.281; 25 x 1024 x 2048 f16, 4000 velocities, K = 50 79.8 -> 73.8; 9 x 613 x 1187 bf16,
-// 260 velocities, K = 52 1.50 -> 1.17; 15 x 4096^2, 600 velocities, K = 50 (12.8 of 14
+// 0.281; 25 x 1024 x 2048 f16, 4000 velocities, K = 50 79.8 -> 65.9 (kPaceVelocities);
+// 25 x 1500^2, 1000 velocities, K = 50 46.3 -> 22.3; 9 x 613 x 1187 bf16,
+// 260 velocities, K = 52 1.50 -> 1.21; 15 x 4096^2, 600 velocities, K = 50 (12.8 of 14
 // images seen) 79.5 -> 80.0, bound by the same path at 20 cycles a load, most
 // of them from L2.  Images and velocities keep their order within a class; the
 // sums of a velocity run in image order and the selection does not depend on
@@ -888,8 +889,8 @@ __device__ __forceinline__ void visit_velocities(
 // several).  All scalar arguments are wave-uniform.
 template <int KM, int PB, int FMT, class Pace>
 __device__ __forceinline__ void search_tile(
-    Pace &&pace, uint32_t *group_lds, int part, int parts, int chunk, const void *__restrict__ planes,
-    const float2 *__restrict__ inv_scale,
+    Pace &&pace, uint32_t *group_lds, int part, int parts, int chunk,
+    const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index, int n_vel, int k_cand, int row, int seg,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
@@ -988,8 +989,8 @@ __device__ __forceinline__ void search_tile(
     // with fewer too: 16 / 12 loads 4.74 / 4.90 and 5.16 / 5.23 ms (15 x 1024^2).
     constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 14 : 16;
     visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
-                                  w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts, chunk,
-                                  finish, full, merge_queue, pace);
+                                  w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts,
+                                  chunk, finish, full, merge_queue, pace);
     do merge_queue();
     while (__any(nq > 0));
 
@@ -1070,8 +1071,9 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_kernel(
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
-    search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride,
-                             vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
+    search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
+                             disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
+                             cand_vel, cand_nobs);
 }
 
 // The single-stack search of frames with too few tiles to fill the GPU: the

@@ -28,9 +28,6 @@ namespace {
 constexpr int TH_NV = 16;          // loads of a batch
 constexpr int TH_STRIP = 4;        // tiles per strip of the tile order
 
-#ifndef KBMI_TH_PER_CU
-#define KBMI_TH_PER_CU KBMI_PERSIST_PER_CU
-#endif
 // One tile: 64 adjacent start pixels of one row, every velocity, with the
 // top-k search's gathers (visit_velocities); each trajectory is scored and
 // appended if nu >= nu_min: one atomic per wave reserves the wave's slots.
@@ -127,7 +124,9 @@ int threshold_grid() {
                 &per_cu, search_threshold_persistent_kernel, 64, 0) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
-        cached[dev] = std::min(per_cu, KBMI_TH_PER_CU) * cus;
+        // (12 and 16 workgroups a CU, which the registers allow, take 19.9 and 19.7 ms
+        // for 19.2 at 15 x 2048^2: each XCD's block outgrows its L2.)
+        cached[dev] = std::min(per_cu, KBMI_PERSIST_PER_CU) * cus;
     }
     return cached[dev];
 }
