@@ -82,6 +82,7 @@ struct BatchJob {
     int dense;                 // 1: strip order (strip tiles wide); 0: block order
     int strip;
     int bs, brows, nbc, nbr;   // block order (PersistMap's fields)
+    int long_walk;
 };
 
 // The launch of a batch: `grid` workgroups, `generations` generations, the
@@ -520,6 +521,9 @@ constexpr int kChunk = 256;           // velocities classified at once
 constexpr int kPaceVelocities = 1024;
 static_assert(kPaceVelocities % kChunk == 0, "a pace stands between two chunks");
 constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales fit the LDS
+inline bool is_long_walk(int64_t n_img, int64_t n_vel, bool f32) {
+    return n_img > 17 && n_vel >= 2 * kPaceVelocities && (f32 || n_img <= kMaxScaleImages);
+}
 constexpr int kScaleWords = 2 * kMaxScaleImages + 2 * 16;
 // LDS words of visit_velocities: a chunk's list and classes, then the inverse
 // scales of 16-bit planes.
@@ -1102,6 +1106,34 @@ __global__ __launch_bounds__(512, 2) void search_split_kernel(
                              cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
 
+// The pacing of one XCD's workgroups.  The wait only shapes timing; no result
+// depends on it.
+struct XcdPace {
+    uint32_t *count;    // arrivals of this XCD
+    uint32_t per_xcd, target;
+    int spin;           // bound of a wait; 0 once one has timed out (the XCD's
+                        // workgroups are not all resident, e.g. beside another launch)
+    __device__ inline XcdPace(uint32_t *sync, int s)
+        : count(sync + (blockIdx.x & 7)), per_xcd(gridDim.x >> 3), target(0), spin(s) {}
+    // This workgroup is n paces further; then wait (a bounded time) until every
+    // workgroup of the XCD is, so that its waves go on together.
+    __device__ inline void pace(int n) {
+        if (threadIdx.x == 0)
+            __hip_atomic_fetch_add(count, (uint32_t)n, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        target += (uint32_t)n * per_xcd;
+        int i = 0;
+        for (; i < spin; ++i) {
+            if (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target)
+                break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+        if (i == spin) spin = 0;
+    }
+};
+// Paces inside a tile of a long walk.
+__device__ inline int paces_inside(int n_vel) { return (n_vel - 1) / kPaceVelocities; }
+
 // The single-stack search in the persistent order (large frames).
 template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_kernel(
@@ -1111,36 +1143,9 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_k
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs, uint32_t *sync) {
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
-    uint32_t *xcd_count = sync + (blockIdx.x & 7);
-    const uint32_t per_xcd = gridDim.x >> 3;
-    int spin = pm.spin;   // 0 once a wait has timed out (the XCD's workgroups are
-                          // not all resident, e.g. beside another launch)
-    uint32_t target = 0;
-    // This workgroup is n waits further; then wait (a bounded time) until every
-    // workgroup of this XCD is, so that its waves go on together.  The wait only
-    // shapes timing; no result depends on it.
-    auto arrive = [&](int n) {
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_add(xcd_count, (uint32_t)n, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        target += (uint32_t)n * per_xcd;
-    };
-    auto wait = [&]() {
-        int i = 0;
-        for (; i < spin; ++i) {
-            if (__hip_atomic_load(xcd_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
-                target)
-                break;
-            __builtin_amdgcn_s_sleep(8);
-        }
-        if (i == spin) spin = 0;
-    };
-    const int paces = pm.long_walk ? (n_vel - 1) / kPaceVelocities : 0;   // inside a tile
+    XcdPace xcd(sync, pm.spin);
     auto pace = [&]() {
-        if (pm.long_walk) {
-            arrive(1);
-            wait();
-        }
+        if (pm.long_walk) xcd.pace(1);
     };
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
@@ -1149,8 +1154,8 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_k
             search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
                                      disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu,
                                      cand_alpha, cand_vel, cand_nobs);
-        arrive(ok ? 1 : 1 + paces);   // generation boundary
-        wait();
+        // Generation boundary.
+        xcd.pace(ok || !pm.long_walk ? 1 : 1 + paces_inside(n_vel));
     }
 }
 
@@ -1175,15 +1180,14 @@ template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel(
     const BatchJob *__restrict__ jobs_, int n_jobs, int generations, int paced, int spin,
     int k_cand, uint32_t *sync) {
-    auto pace = []() {};
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     // The descriptors do not change during the launch: read through the
     // constant address space, their fields stay in scalar registers.
     typedef __attribute__((address_space(4))) const BatchJob CJob;
     const CJob *jobs = (const CJob *)(const void *)jobs_;
-    uint32_t *xcd_count = sync + (blockIdx.x & 7);
     const int grid = (int)gridDim.x;
-    const uint32_t per_xcd = gridDim.x >> 3;
+    // A block job fills its generations, so that every workgroup waits as often.
+    XcdPace xcd(sync, spin);
     for (int gen = 0; gen < generations; ++gen) {
         const int item = gen * grid + (int)blockIdx.x;
         int j = 0;
@@ -1210,24 +1214,17 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel
             const int gl = li / grid;
             ok = gl < block_generations(jb.nbc, jb.nbr) && pm.map(gl, li - gl * grid, row, seg);
         }
+        const bool walk = gen < paced && jb.long_walk != 0;
+        auto pace = [&]() {
+            if (walk) xcd.pace(1);
+        };
         if (ok)
             search_tile<KM, PB, FMT>(
                 pace, lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp,
-                jb.disp_stride, jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu, jb.cand_alpha,
-                jb.cand_vel, jb.cand_nobs);
-        if (gen >= paced) continue;
+                jb.disp_stride, jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu,
+                jb.cand_alpha, jb.cand_vel, jb.cand_nobs);
         // Generation boundary (as in the single-stack persistent search).
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_add(xcd_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t target = (uint32_t)(gen + 1) * per_xcd;
-        int i = 0;
-        for (; i < spin; ++i) {
-            if (__hip_atomic_load(xcd_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
-                target)
-                break;
-            __builtin_amdgcn_s_sleep(8);
-        }
-        if (i == spin) spin = 0;
+        if (gen < paced) xcd.pace(ok || !walk ? 1 : 1 + paces_inside(jb.n_vel));
     }
 }
 

@@ -1086,8 +1086,8 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
     if (workspace_bytes < lay.total)
         return fail(KB_ENOMEM, "workspace needs %zu bytes (got %zu)", lay.total, workspace_bytes);
 
-    // Work items of the launch.  A job of float32 planes large enough for the
-    // paced block order (as kb_search chooses it) starts at a generation
+    // Work items of the launch.  A job large enough for the paced block order
+    // (of float32 planes or a long walk, as kb_search chooses it) starts at a generation
     // boundary and takes its whole block sequence; the others follow densely,
     // tile after tile, those with the longest tiles first.
     const int kc = (int)k_cand;
@@ -1098,7 +1098,9 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
     kb_status st = launch_search_batch(dtype, km, nullptr, shape, &g, s);
     if (st != KB_OK) return st;
     auto blocks = [&](const kb_job &j) {
-        return dtype == KB_F32 && (g / 8) % KBMI_PERSIST_BS == 0 &&
+        const bool order = dtype == KB_F32 || (is_long_walk(j.n_img, j.n_vel, false) &&
+                                               search_waves(km, dtype) == 2);
+        return order && (g / 8) % KBMI_PERSIST_BS == 0 &&
                (j.w + 63) / 64 * j.h >= 4 * (int64_t)g;
     };
     std::vector<int> launch_order(static_cast<size_t>(n_jobs));
@@ -1137,6 +1139,7 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
         const int64_t tiles = (int64_t)d.nseg * j.h;
         const bool block = blocks(j);
         d.dense = block ? 0 : 1;
+        d.long_walk = block && is_long_walk(j.n_img, j.n_vel, dtype == KB_F32) ? 1 : 0;
         d.bs = KBMI_PERSIST_BS;
         d.brows = (g / 8) / d.bs;
         d.nbc = (d.nseg + d.bs - 1) / d.bs;

@@ -52,8 +52,7 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
     // The persistent order pays for float32 planes; the 16-bit search keeps the
     // super-strip order, which measured faster (15 x 2048^2, 600 velocities, K = 50:
     // 14.1 ms against 17.6), except on long walks (kPaceVelocities).
-    const bool long_walk = v.n_img > 17 && v.n_vel >= 2 * kPaceVelocities &&
-                           (KBMI_FMT == KB_F32 || v.n_img <= kMaxScaleImages);
+    const bool long_walk = is_long_walk(v.n_img, v.n_vel, KBMI_FMT == KB_F32);
     if (KBMI_FMT == KB_F32 || (long_walk && search_waves(KM, KBMI_FMT) == 2)) {
         auto kernel = search_persistent_kernel<KM, PB, KBMI_FMT>;
         const int grid =

@@ -763,10 +763,10 @@ def test_tile_shared_by_several_waves_equals_one(torch_dev, h, k, lp):
 
 
 @pytest.mark.parametrize("lp", [None, "f16"])
-def test_long_walk_paced_inside_tiles_equals_batch(torch_dev, lp):
+def test_long_walk_paced_inside_tiles(torch_dev, lp):
     """More than 17 images and 2048 velocities on a frame of several
-    generations, ragged on both sides: bit for bit what a batch, which paces no
-    tile inside, finds."""
+    generations, ragged on both sides, alone and in a batch: bit for bit the
+    best of two searches of half the velocities, which pace no tile inside."""
     from paper_1901_02492_amd import lib
     torch = torch_dev
     dev = torch.device("cuda:0")
@@ -778,7 +778,17 @@ def test_long_walk_paced_inside_tiles_equals_batch(torch_dev, lp):
         lib.make_psi_phi(*d, s.psf, lp=lp)[1:]
     solo = lib.search(src, s.t, s.vel, k, lp_scale=sc)
     out = lib.alloc_candidates(h, w, k, dev)
-    lib.search_batch([dict(planes=src, t=s.t, vel=s.vel, out=out, lp_scale=sc)], k)
+    small = lib.alloc_candidates(h, w, k, dev)
+    half = nv // 2
+    lib.search_batch([dict(planes=src, t=s.t, vel=s.vel[:60], out=small, lp_scale=sc),
+                      dict(planes=src, t=s.t, vel=s.vel, out=out, lp_scale=sc)], k)
     torch.cuda.synchronize()
     for a, b in zip(solo, out):
         assert torch.equal(a, b)
+    a = lib.search(src, s.t, s.vel[:half], k, lp_scale=sc)
+    b = lib.search(src, s.t, s.vel[half:], k, lp_scale=sc)
+    nu, vel = torch.cat([a[0], b[0]], -1), torch.cat([a[2], b[2] + half], -1)
+    order = torch.argsort(vel, dim=-1, stable=True)
+    order = order.gather(-1, torch.argsort(-nu.gather(-1, order), dim=-1, stable=True))[..., :k]
+    assert torch.equal(solo[0], nu.gather(-1, order))
+    assert torch.equal(solo[2], vel.gather(-1, order))
