@@ -454,6 +454,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_rescore_kernel(
         if (s_vj[q] < 0) s_key[q] = (uint64_t)(k_cand - (q - small_quotient(q, inv_k) * k_cand));
     uint32_t *s_sum = s_bin;   // of the ranks (the grouping's bins are free now)
     if (t == 0) *s_sum = 0u;
+    __syncthreads();   // every index is read: scoring puts alphas, which may be negative, there
 
     // Score the pairs in velocity-grouped order, eight images' gathers in
     // flight; the images beyond a multiple of eight go in groups of 4, 2, 1.
