@@ -416,6 +416,7 @@ __global__ __launch_bounds__(LC_THREADS, NB == 16 ? 3 : 1) void lightcurve_group
             s_no[qq] = 0;
             if (rejected) rejected[c0 + qq] = 0;
         }
+    __syncthreads();   // every index is read: the passes put nu, which may be negative, there
     const float inv_k = 1.f / (float)k;
     int n_items = n_sorted;
 #pragma unroll 1

@@ -33,7 +33,7 @@ def _without_assembly(text):
 
 
 @pytest.mark.skipif(shutil.which(CLANG) is None, reason="needs ROCm's clang++")
-@pytest.mark.parametrize("check", ["rescore"])
+@pytest.mark.parametrize("check", ["rescore", "lightcurve"])
 def test_thread_order(check, tmp_path):
     for f in glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.hip")):
         (tmp_path / os.path.basename(f)).write_text(_without_assembly(open(f).read()))
