@@ -1169,8 +1169,8 @@ __global__ void zero_words_kernel(uint32_t *p, int n) {
 // work item g * grid + w (see BatchJob); after the first `paced` generations,
 // which hold the jobs in block order, it waits with the others of its XCD as
 // in the single-stack persistent search.  Without such jobs there is one
-// generation of one workgroup per tile, so that the hardware balances tiles
-// of unlike work; the jobs with the longest tiles come first.  (One launch per
+// generation of one workgroup per tile (batch_grid), so that the hardware balances
+// tiles of unlike work; the jobs with the longest tiles come first.  (One launch per
 // image-count class, each with its own tail, took 1.80 ms for six stacks of 5
 // to 20 images and up to 400 x 500 pixels; one launch takes 0.92 ms.)  Each tile runs exactly the
 // single-stack search, so a stack's results do not depend on what it is

@@ -108,4 +108,17 @@ struct WorkspaceLayout {
 };
 WorkspaceLayout workspace_layout(int64_t n_img, int64_t h, int64_t w, int64_t n_vel);
 
+// The launch of a batched search over `items` work items (tiles) of a device
+// that holds `resident` one-wave workgroups at once: one workgroup a tile, so
+// that the hardware balances tiles of unlike work, unless the order is paced or
+// one launch, whose threads are counted in 32 bits, does not hold as many.
+struct BatchGrid {
+    int grid, generations;   // generation g: items [g grid, (g + 1) grid)
+};
+constexpr int64_t kMaxWaveGroups = (int64_t(1) << 32) / 64 - 1;
+inline BatchGrid batch_grid(int64_t items, int resident, bool paced) {
+    const int64_t grid = paced || items > kMaxWaveGroups ? resident : items;
+    return {(int)grid, (int)((items + grid - 1) / grid)};
+}
+
 }  // namespace kbmi

@@ -1156,8 +1156,9 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
         if (cursor + g > 2147483647LL)
             return fail(KB_EINVAL, "batch holds more work items than one launch");
     }
-    shape.grid = shape.paced > 0 ? g : (int)cursor;
-    shape.generations = (int)((cursor + shape.grid - 1) / shape.grid);
+    const BatchGrid launch = batch_grid(cursor, g, shape.paced > 0);
+    shape.grid = launch.grid;
+    shape.generations = launch.generations;
     shape.sync = reinterpret_cast<uint32_t *>(ws + lay.sync);
     st = staged_copy(ws, host.data(), host.size(), s);
     if (st != KB_OK) return st;

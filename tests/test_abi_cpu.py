@@ -4,6 +4,8 @@ bit for bit, and invalid arguments are rejected before anything is enqueued."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -303,3 +305,13 @@ def test_noalloc_limit_is_the_documented_one(n_img, n_vel):
         base = a(lib.search_workspace_bytes(n_img, 8, 70, nv))
         return a(a(a(base + 8 * n_img) + 16 * nv) + 4 * nv)
     assert need(n_vel) > (8 << 20) >= need(n_vel - 1)   # KB_NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_every_batch_fits_a_launch(tmp_path):
+    exe = str(tmp_path / "check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_1901_02492_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "batch_grid_check.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr

@@ -715,6 +715,29 @@ def test_batch_of_block_and_dense_jobs_equals_solo(torch_dev):
             assert a.tobytes() == b.tobytes()
 
 
+def test_batch_of_more_tiles_than_one_launch_has_workgroups(torch_dev):
+    """2^26 tiles and some (rows of one pixel, one image, 16-bit): each pixel's
+    candidate is the one that a search of its rows alone gives it."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    h, part = (1 << 26) + 100, 1 << 12
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(91)
+    planes = torch.rand((1, h, 1, 2), generator=gen, device=dev).to(torch.float16)
+    scale = torch.ones((1, 2), device=dev)
+    t, vel = np.zeros(1), np.zeros((1, 2))
+    out = lib.alloc_candidates(h, 1, 1, dev)
+    _say(f"case batch of {h} tiles")
+    lib.search_batch([dict(planes=planes, t=t, vel=vel, out=out, lp_scale=scale)], 1)
+    torch.cuda.synchronize()
+    for at in (0, (1 << 25) - 7, h - part):
+        rows = planes[:, at:at + part].contiguous()
+        solo = lib.search(rows, t, vel, 1, lp_scale=scale)
+        for a, b in zip(out, solo):
+            assert torch.equal(a[at:at + part], b)
+
+
 @pytest.mark.parametrize("psf_shape", [(1, 1), (3, 5), (11, 11), (21, 7), (25, 25)])
 def test_planes_do_not_depend_on_the_tile_height(torch_dev, psf_shape):
     """A stack of enough tiles for two rows a thread gives every image bit for
