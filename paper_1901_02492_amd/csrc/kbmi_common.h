@@ -44,7 +44,8 @@ kb_status check_search_args(const void *planes, int32_t dtype, const float *lp_s
 kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_scale,
                            int64_t n_img, int64_t h, int64_t w, int64_t n_vel, int64_t k_cand,
                            float *cand_nu, float *cand_alpha, int32_t *cand_vel,
-                           int16_t *cand_nobs, void *workspace, hipStream_t s);
+                           int16_t *cand_nobs, void *workspace, const Reach &reach,
+                           hipStream_t s);
 
 // One displacement on the device: floor(v * tau + 0.5) as a separate IEEE
 // double multiply, add and floor (no contraction), which rounds exactly as

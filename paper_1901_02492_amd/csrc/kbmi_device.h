@@ -54,6 +54,7 @@ struct StackView {
     int disp_stride;
     const int32_t *vel_index;  // original index of each visited velocity
     int n_vel, k_cand;
+    Reach reach;
     float *cand_nu, *cand_alpha;
     int32_t *cand_vel;
     int16_t *cand_nobs;
@@ -83,6 +84,7 @@ struct BatchJob {
     int strip;
     int bs, brows, nbc, nbr;   // block order (PersistMap's fields)
     int long_walk;
+    Reach reach;
 };
 
 // The launch of a batch: `grid` workgroups, `generations` generations, the
@@ -93,21 +95,25 @@ struct BatchShape {
     uint32_t *sync;
 };
 
-// Waves of a search kernel per SIMD.  16-bit planes take as many as short lists
-// leave registers for: 12 x 700^2, 640 velocities, K = 5 1.469 ms with 2, 1.222 with 3,
-// 0.990 with 4; 19 x 786 x 1693, 640 velocities, K = 20 6.38 with 2, 5.30 with 3.
+// Waves of a search kernel per SIMD.  16-bit planes take as many as a short list
+// leaves registers for, two batches of 16 loads and 16 images' scales beside it
+// (12 x 2048^2 f16, 600 velocities, K = 5 11.7 ms with 2 waves, 8.3 with 3, 7.1 with 4).
+// One more spills: K = 10 with 4 waves 11.3 ms for 8.7 with 3, in bfloat16, whose
+// values take two registers more to widen, 15.1 for 9.4.
 // Float32 planes, whose gathers keep the memory path busy with two, lose as
 // much by the shorter queue: 20 x 500 x 900, K = 10 2.14 ms with 2, 2.19 with 3, 2.43 with 4.
 constexpr int search_waves(int km, int fmt) {
-    return fmt == KB_F32 || km > 20 ? 2 : km <= 12 ? 4 : 3;
+    return fmt == KB_F32 || km > 20 ? 2 : km <= (fmt == KB_F16 ? 8 : 6) ? 4 : 3;
 }
 // Queued candidates per lane before a merge: as many as that many waves' queues
-// and lists leave room for in a CU's LDS.  A merge takes 16; with a queue of 22 more of
-// them are filled when one of the wave's lanes runs full (K = 50, 16 -> 22:
-// 12 x 251 x 301, 400 velocities 0.291 -> 0.281 ms; 25 x 1024 x 2048 f16, 4000
-// velocities 75.2 -> 74.3 ms).
+// and lists leave room for in a CU's LDS, which is given out in pieces of 1280
+// bytes (a queue of 14 takes 11 and leaves room for 11 waves, one of 13 takes 10 and
+// leaves 12: 8 x 1024^2 f16, 600 velocities, K = 10 2.12 -> 1.92 ms).  A merge takes 16;
+// with a queue of 22 more of them are filled when one of the wave's lanes runs
+// full (K = 50, 16 -> 22: 12 x 251 x 301, 400 velocities 0.291 -> 0.281 ms;
+// 25 x 1024 x 2048 f16, 4000 velocities 75.2 -> 74.3 ms).
 constexpr int search_queue(int km, int fmt) {
-    return search_waves(km, fmt) == 4 ? 9 : search_waves(km, fmt) == 3 ? 14 : 22;
+    return search_waves(km, fmt) == 4 ? 9 : search_waves(km, fmt) == 3 ? 13 : 22;
 }
 
 kb_status launch_status(const char *what);
@@ -477,7 +483,7 @@ __device__ inline float lp_value(uint32_t bits16, int fmt) {
 // grow with the image in both axes), so a tile sees a velocity in a prefix
 // 1 .. m of the images: the velocities are sorted into classes by m, a chunk
 // at a time, and each class is visited by a loop with exactly its number of
-// loads, rounded up to even, so that the wait before a batch's sums counts the
+// loads, rounded up to even (class_of), so that the wait before a batch's sums counts the
 // loads behind it (a branch around single loads makes the compiler wait for
 // all: 25 images, float32, 902 -> 1655 ms).  m comes from a binary search in
 // the table's own displacements, a velocity per lane.  A load per image ->
@@ -606,48 +612,55 @@ struct Tile {
     }
 };
 
-// The entries of a list from the q-th on, one held by each lane; q stops at
-// the last.
+// The entries of a list from the q-th on; q stops at the last.  A list in LDS is
+// held an entry by each lane; with `run` not 0 it is run + 0, run + 1, ..
 struct ListCursor {
     const uint32_t *list;
     int n, q;
-    uint32_t held;
-    __device__ inline ListCursor(const uint32_t *l, int count, int from)
-        : list(l), n(count), q(from) {
-        load();
+    uint32_t run, held;
+    __device__ inline ListCursor(const uint32_t *l, uint32_t r, int count, int from)
+        : list(l), n(count), q(from), run(r), held(0) {
+        if (run == 0) load();
     }
     __device__ inline void load() { held = list[min((q & ~63) + wave_lane(), n - 1)]; }
     __device__ inline uint32_t entry() const {
+        if (run != 0) return run + (uint32_t)q;
         return (uint32_t)__builtin_amdgcn_readlane((int)held, q & 63);
     }
     __device__ inline void step() {
         if (q + 1 < n) {
             ++q;
-            if ((q & 63) == 0) load();
+            if (run == 0 && (q & 63) == 0) load();
         }
     }
 };
 
-// The velocities of the class in t.list from the q-th on, n of them: calls
-// finish(j, P, F, n_obs) for each with the velocity's original index j and the
-// sums of this lane's pixel, until full() (the selection's queue may not hold
-// two more) or the list ends; returns the next q.
-//   NV     loads of a batch.  The last of an odd class is not real: a
-//          zero-length buffer, whose base is never dereferenced
-//   MULTI  a velocity takes several batches (more images than NV)
+enum { kOne, kMany };
+
+// The velocities of the class in t.list (with RUNS: or of the run, if not 0) from
+// the q-th on, n of them: calls finish(j, P, F, n_obs) for each with the
+// velocity's original index j and the sums of this lane's pixel, until full()
+// (the selection's queue may not hold two more) or the list ends; returns the
+// next q.
+//   NV     loads of a batch.  Where a velocity of an even class sees one image
+//          less, the last load is not real: a zero-length buffer, whose base is
+//          never dereferenced
+//   PARTS  batches of a velocity: one or several
 // Two batches are in flight: the gathers of the next are issued before the
 // current one is summed and scored, and the table entries of the one after are
 // fetched behind them, into the registers the next one's just left.  Rows of
 // the displaced window are in the frame for every real load, columns are cut by
 // the buffer's range check.  Fetched entries may pass the end of the table by
 // up to 14 (the order array lies there); their loads are not real.
-template <int NV, bool MULTI, int FMT, class Finish, class Full>
-__device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, int n, int q,
-                                           Finish &&finish, Full &&full) {
+template <int NV, int PARTS, int FMT, bool RUNS, class Finish, class Full>
+__device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, uint32_t run_, int n,
+                                           int q, Finish &&finish, Full &&full) {
     typedef typename Tile<FMT>::LoadT LoadT;
+    constexpr bool MULTI = PARTS != kOne;
     q = __builtin_amdgcn_readfirstlane(q);   // (uniform: said again where it is lost)
     n = __builtin_amdgcn_readfirstlane(n);
-    ListCursor cur(t.list, n, q);
+    const uint32_t run = RUNS ? __builtin_amdgcn_readfirstlane(run_) : 0u;
+    ListCursor cur(t.list, run, n, q);
     // The entries in e: those of velocity `place` of the chunk, part part_f of
     // parts_f, of which left_f are visible.
     int part_f = 0, parts_f = 1, left_f = 0, j_f = 0;
@@ -678,10 +691,23 @@ __device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, int n, in
 #pragma unroll
         for (int b = 0; b < NV; ++b) {
             const uint64_t off = ((uint64_t)(uint32_t)e[b].w << 32) | (uint32_t)e[b].z;
-            const bool real = (MULTI || b == NV - 1) ? b < left_f : true;
+            const bool real = (MULTI || (NV % 2 == 0 && b == NV - 1)) ? b < left_f : true;
             v[b] = t.load(t.row0 + off, real ? t.row_bytes : 0u, e[b].x);
         }
     };
+    // 16-bit planes: the inverse scales of one batch's images stay in vector
+    // registers.  (Read from the LDS for each velocity they would make its sums
+    // wait for the entries just fetched, which the scalar path returns in any
+    // order: 12 x 4096^2 f16, 600 velocities, K = 50 54.9 -> 51.5 ms.)
+    constexpr bool kHeld = FMT != KB_F32 && !MULTI;
+    float held[2 * NV];
+    if constexpr (kHeld) {
+#pragma unroll
+        for (int b = 0; b < 2 * NV; ++b) {
+            held[b] = t.scale[b];
+            asm volatile("" : "+v"(held[b]));
+        }
+    }
     i32x4 e[NV];
     LoadT va[NV], vb[NV];
     enter();
@@ -699,13 +725,16 @@ __device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, int n, in
         advance();
         fetch(e);
         __builtin_amdgcn_sched_barrier(0);
+        const float *sc = nullptr;
+        if constexpr (FMT != KB_F32) sc = t.scale + 2 * (NV * part);
 #pragma unroll
         for (int b = 0; b < NV; ++b) {
             if constexpr (FMT == KB_F32) {
                 sum.add(cur_v[b]);
+            } else if constexpr (kHeld) {
+                sum.add(cur_v[b], held[2 * b], held[2 * b + 1]);
             } else {
-                const float *sc = t.scale + 2 * (NV * part + b);
-                sum.add(cur_v[b], sc[0], sc[1]);
+                sum.add(cur_v[b], sc[2 * b], sc[2 * b + 1]);
             }
         }
         if (!MULTI || ++part == parts_c) {
@@ -758,7 +787,22 @@ __device__ __forceinline__ int visit_serial(const Tile<FMT> &t, const float2 *in
     return q;
 }
 
-#define KB_BATCH_LIST(X) X(2) X(4) X(6) X(8) X(10) X(12) X(14) X(16)
+#define KB_BATCH_LIST(X) \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(10) X(12) X(14) X(16)
+
+// The class of m visible images of `all`: the loads of its batch, or kMulti and
+// those of each of several.  One batch's loads are rounded up to even, so that
+// a frame whose edges cut trajectories has half the classes to begin anew, but
+// for the velocities that all of up to 8 images see: on large frames these are
+// most, and a load in 8 is worth it (8 x 4096^2 float32, 600 velocities, K = 5 49.5 ->
+// 46.5 ms; exact classes throughout: 12 x 300^2 0.410 -> 0.427 ms).
+constexpr int kMulti = 15;
+template <int MAXNV>
+__device__ inline int class_of(int m, int all) {
+    const int parts = (m + MAXNV - 1) / MAXNV;
+    if (parts > 1) return kMulti + ((m + parts - 1) / parts + 1) / 2 * 2;
+    return m == all && m <= 8 ? m : (m + 1) / 2 * 2;
+}
 
 // The velocities of one tile (start row `row`, start columns seg*64 ..
 // seg*64+63) that wave `part` of `parts` takes, every parts-th chunk of
@@ -767,12 +811,12 @@ __device__ __forceinline__ int visit_serial(const Tile<FMT> &t, const float2 *in
 // where full(), and pace() after every kPaceVelocities velocities.  All scalar
 // arguments are wave-uniform.  words: kVisitWords of LDS; MAXNV: loads of a
 // batch, at most.
-template <int FMT, int MAXNV, class Finish, class Full, class Drain, class Pace>
+template <int FMT, int MAXNV, bool RUNS, class Finish, class Full, class Drain, class Pace>
 __device__ __forceinline__ void visit_velocities(
     uint32_t *words, const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
-    const int32_t *__restrict__ vel_index, int n_vel, int row, int seg, int part, int parts,
-    int chunk, Finish &&finish, Full &&full, Drain &&drain, Pace &&pace) {
+    const int32_t *__restrict__ vel_index, int n_vel, const Reach &reach, int row, int seg,
+    int part, int parts, int chunk, Finish &&finish, Full &&full, Drain &&drain, Pace &&pace) {
     const int lane = wave_lane();
     Tile<FMT> t;
     t.row_bytes = (uint32_t)w * Tile<FMT>::kPix;
@@ -815,43 +859,52 @@ __device__ __forceinline__ void visit_velocities(
         else t.start.add(v0, inv_scale[0].x, inv_scale[0].y);
     }
     const int ni = n_img - 1;
-    constexpr int kMulti = MAXNV / 2;    // classes: 0, NV / 2, kMulti + NV / 2 of several parts
+    // A tile that no trajectory leaves sees every velocity in every image: one
+    // class, in order, with no list and no look at the table, of which every
+    // lane reads a line of its own.  (16-bit planes and large float32 frames, with
+    // lists that leave registers for it: 15 x 2048^2 f16, 600 velocities, K = 10 9.95 -> 9.3
+    // ms; 8 x 2048^2 float32, K = 1 12.2 -> 11.2.  Small float32 frames have few such
+    // tiles and lose 2 % by the question: 12 x 251 x 301, K = 5.)
+    const bool inside = RUNS && ni > 0 && row + reach.y_lo >= 0 && row + reach.y_hi < h &&
+                        x_last + reach.x_lo >= 0 && x_first + reach.x_hi < w;
+    const uint32_t run = inside ? (uint32_t)ni << 16 : 0u;
+    if (inside && parts == 1) chunk = kPaceVelocities;
     for (int v0 = part * chunk; v0 < n_vel; v0 += parts * chunk) {
         if (v0 > 0 && v0 % kPaceVelocities == 0) pace();
         const int nc = min(chunk, n_vel - v0);
-        uint32_t present = 0;   // classes of the chunk's velocities
-        for (int k0 = 0; k0 < nc; k0 += 64) {
-            const int k = k0 + lane;
-            const GatherEntry *entries = disp + (size_t)(v0 + min(k, nc - 1)) * disp_stride;
-            auto visible = [&](int i) {
-                const int dx = entries[i].dx, dy = entries[i].dy;
-                return (unsigned)(row + dy) < (unsigned)h && x_last + dx >= 0 &&
-                       x_first + dx < w;
-            };
-            int m = ni, out = ni;
-            if (ni > 0 && !visible(ni)) m = 0;
-            while (__any(out - m > 1)) {
-                const int i = (m + out) >> 1;
-                const bool see = visible(i);
-                if (out - m > 1) (see ? m : out) = i;
-            }
-            const int parts = (m + MAXNV - 1) / MAXNV;
-            const int nv = parts <= 1 ? (m + 1) / 2 : ((m + parts - 1) / parts + 1) / 2;
-            const int c = nv + (parts > 1 ? kMulti : 0);
-            t.seen[k] = (uint16_t)m;
-            t.cls[k] = (uint8_t)c;
-            uint64_t todo = __ballot(k < nc);
-            while (todo != 0) {
-                const int c0 = __builtin_amdgcn_readlane(c, __builtin_ctzll(todo));
-                present |= 1u << c0;
-                todo &= ~__ballot(c == c0);
+        uint32_t present = inside ? 1u << class_of<MAXNV>(ni, ni) : 0u;   // the chunk's classes
+        if (!inside) {
+            for (int k0 = 0; k0 < nc; k0 += 64) {
+                const int k = k0 + lane;
+                const GatherEntry *entries = disp + (size_t)(v0 + min(k, nc - 1)) * disp_stride;
+                auto visible = [&](int i) {
+                    const int dx = entries[i].dx, dy = entries[i].dy;
+                    return (unsigned)(row + dy) < (unsigned)h && x_last + dx >= 0 &&
+                           x_first + dx < w;
+                };
+                int m = ni, out = ni;
+                if (ni > 0 && !visible(ni)) m = 0;
+                while (__any(out - m > 1)) {
+                    const int i = (m + out) >> 1;
+                    const bool see = visible(i);
+                    if (out - m > 1) (see ? m : out) = i;
+                }
+                const int c = class_of<MAXNV>(m, ni);
+                t.seen[k] = (uint16_t)m;
+                t.cls[k] = (uint8_t)c;
+                uint64_t todo = __ballot(k < nc);
+                while (todo != 0) {
+                    const int c0 = __builtin_amdgcn_readlane(c, __builtin_ctzll(todo));
+                    present |= 1u << c0;
+                    todo &= ~__ballot(c == c0);
+                }
             }
         }
         while (present != 0) {
             const int c0 = __builtin_ctz(present);
             present &= present - 1;
-            int n = 0;
-            for (int k0 = 0; k0 < nc; k0 += 64) {
+            int n = inside ? nc : 0;
+            for (int k0 = 0; k0 < nc && !inside; k0 += 64) {
                 const int k = k0 + lane;
                 const bool hit = k < nc && t.cls[k] == c0;
                 const uint64_t b = __ballot(hit);
@@ -871,12 +924,13 @@ __device__ __forceinline__ void visit_velocities(
                         finish(t.visit[v0 + k], t.start.P, t.start.F, t.start.count());
                     } while (q < n && !full());
                 }
-#define KB_CASE(NV)                                                                      \
-    if constexpr (NV <= MAXNV) {                                                         \
-        if (c0 == NV / 2) q = visit_class<NV, false, FMT>(t, v0, n, q, finish, full);    \
-    }                                                                                    \
-    if constexpr (NV <= MAXNV && NV > MAXNV / 2) {                                       \
-        if (c0 == kMulti + NV / 2) q = visit_class<NV, true, FMT>(t, v0, n, q, finish, full); \
+#define KB_CASE(NV)                                                                          \
+    if constexpr (NV <= MAXNV) {                                                             \
+        if (c0 == NV) q = visit_class<NV, kOne, FMT, RUNS>(t, v0, run, n, q, finish, full);  \
+    }                                                                                        \
+    if constexpr (NV % 2 == 0 && NV <= MAXNV && NV > MAXNV / 2) {                            \
+        if (c0 == kMulti + NV)                                                               \
+            q = visit_class<NV, kMany, FMT, RUNS>(t, v0, run, n, q, finish, full);           \
     }
                 KB_BATCH_LIST(KB_CASE)
 #undef KB_CASE
@@ -891,14 +945,14 @@ __device__ __forceinline__ void visit_velocities(
 // by a workgroup of `parts` waves (a power of two), of which this is wave
 // `part`.  lds: search_lds_words for each wave (and parts / 2 lists, for
 // several).  All scalar arguments are wave-uniform.
-template <int KM, int PB, int FMT, class Pace>
+template <int KM, int PB, int FMT, bool RUNS, class Pace>
 __device__ __forceinline__ void search_tile(
     Pace &&pace, uint32_t *group_lds, int part, int parts, int chunk,
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale,
     int n_img, int h, int w, const GatherEntry *__restrict__ disp, int disp_stride,
-    const int32_t *__restrict__ vel_index, int n_vel, int k_cand, int row, int seg,
-    float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
-    int16_t *__restrict__ cand_nobs) {
+    const int32_t *__restrict__ vel_index, int n_vel, const Reach &reach, int k_cand, int row,
+    int seg, float *__restrict__ cand_nu, float *__restrict__ cand_alpha,
+    int32_t *__restrict__ cand_vel, int16_t *__restrict__ cand_nobs) {
     uint32_t *lds = group_lds + part * search_lds_words<KM, PB>();
     uint32_t *q_hi = lds;
     uint32_t *q_lo = lds + PB * 64;
@@ -987,14 +1041,17 @@ __device__ __forceinline__ void search_tile(
     auto full = [&]() { return __any(nq >= PB - 1) != 0; };
 
     // Loads of a batch: two batches lie beside the list.  16-bit planes, 25
-    // images, K = 50: 16 / 12 / 8 loads 73.8 / 77.0 / 87.9 ms.  K = 52 spills with 16,
-    // and 12 split the usual 14 images: 16 / 14 / 12 loads 24.4 / 23.0 / 29.1 ms (15 x
-    // 2048^2, 900 velocities), 1.292 / 1.212 / 1.182 (9 x 613 x 1187).  K = 60 and 64 spill
-    // with fewer too: 16 / 12 loads 4.74 / 4.90 and 5.16 / 5.23 ms (15 x 1024^2).
-    constexpr int kMaxNv = KM <= 50 ? 16 : FMT == KB_F32 ? 8 : KM <= 56 ? 14 : 16;
-    visit_velocities<FMT, kMaxNv>(lds + search_queue_words<KM, PB>(), planes, inv_scale, n_img, h,
-                                  w, disp, disp_stride, vel_index, n_vel, row, seg, part, parts,
-                                  chunk, finish, full, merge_queue, pace);
+    // images, K = 50: 16 / 12 / 8 loads 73.8 / 77.0 / 87.9 ms.  Lists of 52 and more
+    // spill with 16, but a limit below costs more where images fill a batch of 16
+    // (K = 52, 600 velocities, 16 / 14 loads: 16 x 2048^2 f16 14.4 / 18.9 ms, 17 x
+    // 2048^2 14.6 / 19.5, 15 x 2048^2 13.7 / 13.5, bfloat16 15.5 / 14.9).  Float32: K = 52
+    // to 64 in batches of 8.
+    constexpr int kMaxNv = KM <= 50 || FMT != KB_F32 ? 16 : 8;
+    constexpr bool kRuns = RUNS && 3 * KM + 4 * kMaxNv <= 200;   // (K <= 44)
+    visit_velocities<FMT, kMaxNv, kRuns>(lds + search_queue_words<KM, PB>(), planes, inv_scale,
+                                         n_img, h, w, disp, disp_stride, vel_index, n_vel, reach,
+                                         row, seg, part, parts, chunk, finish, full, merge_queue,
+                                         pace);
     do merge_queue();
     while (__any(nq > 0));
 
@@ -1068,16 +1125,16 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride,
     const int32_t *__restrict__ vel_index,
-    int n_vel, int k_cand, TileMap tiles, float *__restrict__ cand_nu,
+    int n_vel, Reach reach, int k_cand, TileMap tiles, float *__restrict__ cand_nu,
     float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs) {
     auto pace = []() {};
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
-    search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
-                             disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu, cand_alpha,
-                             cand_vel, cand_nobs);
+    search_tile<KM, PB, FMT, (FMT != KB_F32)>(
+        pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp, disp_stride, vel_index,
+        n_vel, reach, k_cand, row, seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
 }
 
 // The single-stack search of frames with too few tiles to fill the GPU: the
@@ -1093,7 +1150,8 @@ template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(512, 2) void search_split_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride,
-    const int32_t *__restrict__ vel_index, int n_vel, int k_cand, TileMap tiles, int chunk,
+    const int32_t *__restrict__ vel_index, int n_vel, Reach reach, int k_cand, TileMap tiles,
+    int chunk,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs) {
     auto pace = []() {};
@@ -1101,9 +1159,10 @@ __global__ __launch_bounds__(512, 2) void search_split_kernel(
     int row, seg;
     tiles.map(blockIdx.x, row, seg);
     const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    search_tile<KM, PB, FMT>(pace, split_lds, part, (int)blockDim.x >> 6, chunk, planes, inv_scale,
-                             n_img, h, w, disp, disp_stride, vel_index, n_vel, k_cand, row, seg,
-                             cand_nu, cand_alpha, cand_vel, cand_nobs);
+    search_tile<KM, PB, FMT, false>(pace, split_lds, part, (int)blockDim.x >> 6, chunk, planes,
+                                    inv_scale, n_img, h, w, disp, disp_stride, vel_index, n_vel,
+                                    reach, k_cand, row, seg, cand_nu, cand_alpha, cand_vel,
+                                    cand_nobs);
 }
 
 // The pacing of one XCD's workgroups.  The wait only shapes timing; no result
@@ -1139,7 +1198,7 @@ template <int KM, int PB, int FMT>
 __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_kernel(
     const void *__restrict__ planes, const float2 *__restrict__ inv_scale, int n_img, int h,
     int w, const GatherEntry *__restrict__ disp, int disp_stride,
-    const int32_t *__restrict__ vel_index, int n_vel, int k_cand, PersistMap pm,
+    const int32_t *__restrict__ vel_index, int n_vel, Reach reach, int k_cand, PersistMap pm,
     float *__restrict__ cand_nu, float *__restrict__ cand_alpha, int32_t *__restrict__ cand_vel,
     int16_t *__restrict__ cand_nobs, uint32_t *sync) {
     __shared__ __align__(16) uint32_t lds[search_lds_words<KM, PB>()];
@@ -1151,9 +1210,9 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_persistent_k
         int row, seg;
         const bool ok = pm.map(gen, (int)blockIdx.x, row, seg);
         if (ok)
-            search_tile<KM, PB, FMT>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w, disp,
-                                     disp_stride, vel_index, n_vel, k_cand, row, seg, cand_nu,
-                                     cand_alpha, cand_vel, cand_nobs);
+            search_tile<KM, PB, FMT, true>(pace, lds, 0, 1, kChunk, planes, inv_scale, n_img, h, w,
+                                           disp, disp_stride, vel_index, n_vel, reach, k_cand, row,
+                                           seg, cand_nu, cand_alpha, cand_vel, cand_nobs);
         // Generation boundary.
         xcd.pace(ok || !pm.long_walk ? 1 : 1 + paces_inside(n_vel));
     }
@@ -1214,14 +1273,15 @@ __global__ __launch_bounds__(64, search_waves(KM, FMT)) void search_batch_kernel
             const int gl = li / grid;
             ok = gl < block_generations(jb.nbc, jb.nbr) && pm.map(gl, li - gl * grid, row, seg);
         }
+        const Reach reach{jb.reach.x_lo, jb.reach.x_hi, jb.reach.y_lo, jb.reach.y_hi};
         const bool walk = gen < paced && jb.long_walk != 0;
         auto pace = [&]() {
             if (walk) xcd.pace(1);
         };
         if (ok)
-            search_tile<KM, PB, FMT>(
+            search_tile<KM, PB, FMT, (FMT != KB_F32)>(
                 pace, lds, 0, 1, kChunk, jb.planes, jb.inv_scale, jb.n_img, jb.h, jb.w, jb.disp,
-                jb.disp_stride, jb.vel_index, jb.n_vel, k_cand, row, seg, jb.cand_nu,
+                jb.disp_stride, jb.vel_index, jb.n_vel, reach, k_cand, row, seg, jb.cand_nu,
                 jb.cand_alpha, jb.cand_vel, jb.cand_nobs);
         // Generation boundary (as in the single-stack persistent search).
         if (gen < paced) xcd.pace(ok || !walk ? 1 : 1 + paces_inside(jb.n_vel));

@@ -79,6 +79,20 @@ void displacement_table(const double *t, int64_t n_img, const double *vel, int64
     }
 }
 
+Reach reach_of(const double *t, int64_t n_img, const double *vel, int64_t n_vel, int64_t h,
+               int64_t w) {
+    Reach r{0, 0, 0, 0};
+    const double tau = t[n_img - 1] - t[0];
+    for (int64_t j = 0; j < n_vel; ++j) {
+        const int32_t dx = offset_of(vel[2 * j], tau, w), dy = offset_of(vel[2 * j + 1], tau, h);
+        r.x_lo = std::min(r.x_lo, dx);
+        r.x_hi = std::max(r.x_hi, dx);
+        r.y_lo = std::min(r.y_lo, dy);
+        r.y_hi = std::max(r.y_hi, dy);
+    }
+    return r;
+}
+
 #ifndef KBMI_HILBERT_ORDER
 #define KBMI_HILBERT_ORDER 1
 #endif

@@ -89,6 +89,15 @@ static_assert(sizeof(GatherEntry) == 16, "gather entries are fetched as 16-byte 
 // whose column is outside the frame too), then the
 // original index of each visited velocity (int32 [n_vel]).
 int64_t table_stride(int64_t n_img);
+
+// How far trajectories go: the smallest and largest displacement of any
+// velocity in any image, clamped to the frame as the table's are.  (A velocity's
+// displacements start at 0 and grow with the image, so the last image's do.)
+struct Reach {
+    int32_t x_lo, x_hi, y_lo, y_hi;
+};
+Reach reach_of(const double *t, int64_t n_img, const double *vel, int64_t n_vel, int64_t h,
+               int64_t w);
 size_t table_bytes(int64_t n_img, int64_t n_vel);
 size_t order_bytes(int64_t n_vel);
 

@@ -653,7 +653,8 @@ kb_status check_search_args(const void *planes, int32_t dtype, const float *lp_s
 kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_scale,
                            int64_t n_img, int64_t h, int64_t w, int64_t n_vel, int64_t k_cand,
                            float *cand_nu, float *cand_alpha, int32_t *cand_vel,
-                           int16_t *cand_nobs, void *workspace, hipStream_t s) {
+                           int16_t *cand_nobs, void *workspace, const Reach &reach,
+                           hipStream_t s) {
     char *wsb = static_cast<char *>(workspace);
     const WorkspaceLayout lay = workspace_layout(n_img, h, w, n_vel);
     StackView sv;
@@ -667,6 +668,7 @@ kb_status launch_search_in(const void *planes, int32_t dtype, const float *lp_sc
     sv.vel_index = reinterpret_cast<const int32_t *>(wsb + lay.order);
     sv.n_vel = (int)n_vel;
     sv.k_cand = (int)k_cand;
+    sv.reach = reach;
     sv.cand_nu = cand_nu;
     sv.cand_alpha = cand_alpha;
     sv.cand_vel = cand_vel;
@@ -946,7 +948,8 @@ kb_status kb_search(const void *planes, int32_t dtype, const float *lp_scale, in
     st = upload_table(t, n_img, vel, n_vel, h, w, dtype == KB_F32 ? 8 : 4, workspace, s);
     if (st != KB_OK) return st;
     return launch_search_in(planes, dtype, lp_scale, n_img, h, w, n_vel, k_cand, cand_nu,
-                            cand_alpha, cand_vel, cand_nobs, workspace, s);
+                            cand_alpha, cand_vel, cand_nobs, workspace,
+                            reach_of(t, n_img, vel, n_vel, h, w), s);
 }
 
 kb_status kb_topk(const float *psi_phi_f32, int64_t n_img, int64_t h, int64_t w,
@@ -1135,6 +1138,7 @@ kb_status kb_search_batch(const kb_job *jobs, int64_t n_jobs, int32_t dtype, int
         d.w = (int)j.w;
         d.disp_stride = (int)table_stride(j.n_img);
         d.n_vel = (int)j.n_vel;
+        d.reach = reach_of(j.t, j.n_img, j.vel, j.n_vel, j.h, j.w);
         d.nseg = (int)((j.w + 63) / 64);
         d.strip = d.nseg < KBMI_STRIP_TILES ? d.nseg : KBMI_STRIP_TILES;
         const int64_t tiles = (int64_t)d.nseg * j.h;

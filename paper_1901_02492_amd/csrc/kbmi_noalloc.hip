@@ -216,7 +216,8 @@ kb_status kb_search_noalloc(const void *planes, int32_t dtype, const float *lp_s
     st = launch_status("table_kernel");
     if (st != KB_OK) return st;
     return launch_search_in(planes, dtype, lp_scale, n_img, h, w, n_vel, k_cand, cand_nu,
-                            cand_alpha, cand_vel, cand_nobs, ws, s);
+                            cand_alpha, cand_vel, cand_nobs, ws,
+                            reach_of(t, n_img, vel, n_vel, h, w), s);
 }
 
 }  // extern "C"

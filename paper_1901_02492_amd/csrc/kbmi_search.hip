@@ -77,8 +77,8 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
             if (st != KB_OK) return st;
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, v.planes, v.inv_scale,
                                v.n_img, v.h, v.w, v.disp, v.disp_stride, v.vel_index, v.n_vel,
-                               v.k_cand, pm, v.cand_nu, v.cand_alpha, v.cand_vel, v.cand_nobs,
-                               v.sync);
+                               v.reach, v.k_cand, pm, v.cand_nu, v.cand_alpha, v.cand_vel,
+                               v.cand_nobs, v.sync);
             return launch_status("search_persistent_kernel");
         }
     }
@@ -102,14 +102,14 @@ kb_status launch_one(const StackView &v, hipStream_t s) {
         hipLaunchKernelGGL((search_split_kernel<KM, PB, KBMI_FMT>), dim3(tm.nblocks),
                            dim3(64 * parts), (search_split_lds_bytes<KM, PB>(parts)), s, v.planes,
                            v.inv_scale, v.n_img, v.h, v.w, v.disp, v.disp_stride, v.vel_index,
-                           v.n_vel, v.k_cand, tm, chunk, v.cand_nu, v.cand_alpha, v.cand_vel,
-                           v.cand_nobs);
+                           v.n_vel, v.reach, v.k_cand, tm, chunk, v.cand_nu, v.cand_alpha,
+                           v.cand_vel, v.cand_nobs);
         return launch_status("search_split_kernel");
     }
     hipLaunchKernelGGL((search_kernel<KM, PB, KBMI_FMT>), dim3(tm.nblocks), dim3(64), 0, s,
                        v.planes, v.inv_scale, v.n_img, v.h, v.w, v.disp, v.disp_stride,
-                       v.vel_index, v.n_vel, v.k_cand, tm, v.cand_nu, v.cand_alpha, v.cand_vel,
-                       v.cand_nobs);
+                       v.vel_index, v.n_vel, v.reach, v.k_cand, tm, v.cand_nu, v.cand_alpha,
+                       v.cand_vel, v.cand_nobs);
     return launch_status("search_kernel");
 }
 

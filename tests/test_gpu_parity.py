@@ -715,6 +715,35 @@ def test_batch_of_block_and_dense_jobs_equals_solo(torch_dev):
             assert a.tobytes() == b.tobytes()
 
 
+@pytest.mark.parametrize("lp", [None, "f16", "bf16"])
+@pytest.mark.parametrize("n,nv", [(2, 5), (4, 6), (7, 12), (8, 20), (16, 40), (18, 8)])
+def test_tiles_that_no_trajectory_leaves(torch_dev, n, nv, lp):
+    """Slow velocities on a frame with tiles inside and at its edges, alone and
+    in a batch: bit for bit the lists that a search with one more velocity
+    gives, whose trajectories leave every tile."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    h, w = 131, 4099
+    s = synth.random_stack(97, n=n, h=h, w=w, n_vel=nv, k=nv, psf_size=5, vmax=9.0)
+    _say(f"case inside N={n} V={nv} lp={lp}")
+    d = (torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask))
+    src, sc = (lib.make_psi_phi(*d, s.psf), None) if lp is None else \
+        lib.make_psi_phi(*d, s.psf, lp=lp)[1:]
+    solo = lib.search(src, s.t, s.vel, nv, lp_scale=sc)
+    out = lib.alloc_candidates(h, w, nv, dev)
+    lib.search_batch([dict(planes=src, t=s.t, vel=s.vel, out=out, lp_scale=sc)], nv)
+    far = np.concatenate([s.vel, [[1e6, 1e6]]])
+    more = lib.search(src, s.t, far, nv + 1, lp_scale=sc)
+    torch.cuda.synchronize()
+    rest = torch.argsort((more[2] == nv).to(torch.uint8), dim=-1, stable=True)[..., :nv]
+    for a, b, c in zip(solo, out, more):
+        assert torch.equal(a, b)
+        assert torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a,
+                           (c.view(torch.int32) if c.dtype == torch.float32 else c)
+                           .gather(-1, rest))
+
+
 def test_batch_of_more_tiles_than_one_launch_has_workgroups(torch_dev):
     """2^26 tiles and some (rows of one pixel, one image, 16-bit): each pixel's
     candidate is the one that a search of its rows alone gives it."""
