@@ -526,11 +526,12 @@ constexpr int kChunk = 256;           // velocities classified at once
 // 73.8 -> 65.9 ms, 25 x 4096^2 757 -> 608, 25 x 2048 x 4096, 3000 velocities 272 -> 228.
 constexpr int kPaceVelocities = 1024;
 static_assert(kPaceVelocities % kChunk == 0, "a pace stands between two chunks");
-constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales fit the LDS
+constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales lie in the LDS
 inline bool is_long_walk(int64_t n_img, int64_t n_vel, bool f32) {
     return n_img > 17 && n_vel >= 2 * kPaceVelocities && (f32 || n_img <= kMaxScaleImages);
 }
-constexpr int kScaleWords = 2 * kMaxScaleImages + 2 * 16;
+constexpr int kHeldScaleWords = 2 * kMaxScaleImages + 2 * 16;
+constexpr int kScaleWords = kHeldScaleWords + 2 * 16;   // and those of one batch of later images
 // LDS words of visit_velocities: a chunk's list and classes, then the inverse
 // scales of 16-bit planes.
 constexpr int kVisitWords = kChunk + kChunk / 2 + kChunk / 4 + kScaleWords;
@@ -601,10 +602,20 @@ struct Tile {
     uint32_t *list;         // LDS: velocities of the class being visited
     uint16_t *seen;         // LDS: images a velocity is visible in, image 0 apart
     uint8_t *cls;           // LDS: its class
-    const float *scale;     // LDS: inverse scales, image i at 2 (i - 1)
+    float *scale;           // LDS: inverse scales, image i at 2 (i - 1), up to kMaxScaleImages
+    const float *more_scale;   // the same of all images, in memory
     int x;                  // this lane's start column
     PixelSums<FMT> start;   // its pixel's sums in image 0
 
+    // Inverse scales of the images from i on (0-based after image 0), nv of them.
+    __device__ inline const float *scales(int i, int nv) const {
+        if (i + nv <= kMaxScaleImages) return scale + 2 * i;
+        float *own = scale + kHeldScaleWords;
+        const int q = wave_lane();
+        if (q < 2 * nv) own[q] = i + q / 2 < n_img - 1 ? more_scale[2 * i + q] : 0.f;
+        wave_sync();
+        return own;
+    }
     __device__ inline LoadT load(uint64_t base, uint32_t bytes, int dx) const {
         const i32x4 rs = buffer_words(base, bytes);
         if constexpr (FMT == KB_F32) return raw_load_b64(rs, (x + dx) * (int)kPix, 0, 0);
@@ -635,7 +646,7 @@ struct ListCursor {
     }
 };
 
-enum { kOne, kMany };
+enum { kOne, kMany, kManyMore };
 
 // The velocities of the class in t.list (with RUNS: or of the run, if not 0) from
 // the q-th on, n of them: calls finish(j, P, F, n_obs) for each with the
@@ -645,7 +656,8 @@ enum { kOne, kMany };
 //   NV     loads of a batch.  Where a velocity of an even class sees one image
 //          less, the last load is not real: a zero-length buffer, whose base is
 //          never dereferenced
-//   PARTS  batches of a velocity: one or several
+//   PARTS  batches of a velocity: one; several, of images whose scales the LDS
+//          holds; several, also of later images
 // Two batches are in flight: the gathers of the next are issued before the
 // current one is summed and scored, and the table entries of the one after are
 // fetched behind them, into the registers the next one's just left.  Rows of
@@ -726,7 +738,8 @@ __device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, uint32_t 
         fetch(e);
         __builtin_amdgcn_sched_barrier(0);
         const float *sc = nullptr;
-        if constexpr (FMT != KB_F32) sc = t.scale + 2 * (NV * part);
+        if constexpr (PARTS == kManyMore) sc = t.scales(NV * part, NV);
+        else if constexpr (FMT != KB_F32) sc = t.scale + 2 * (NV * part);
 #pragma unroll
         for (int b = 0; b < NV; ++b) {
             if constexpr (FMT == KB_F32) {
@@ -754,37 +767,6 @@ __device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, uint32_t 
         step(vb, va);
     } while (q < n && !full());
     return min(q, n);
-}
-
-// Every velocity of one tile in the same way without classes: 16-bit planes
-// of more images than the LDS holds scales for.
-template <int FMT, class Finish, class Full>
-__device__ __forceinline__ int visit_serial(const Tile<FMT> &t, const float2 *inv_scale,
-                                            int n_vel, int q, Finish &&finish, Full &&full) {
-    constexpr int NB = 8;
-    typedef typename Tile<FMT>::LoadT LoadT;
-    do {
-        const const_i32x4 *row =
-            (const const_i32x4 *)(const void *)(t.disp + (size_t)q * t.stride);
-        PixelSums<FMT> sum;
-        for (int i0 = 0; i0 < t.n_img; i0 += NB) {   // (the row is padded to 16 entries)
-            LoadT v[NB];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const i32x4 e = row[i0 + b];
-                const uint64_t off = ((uint64_t)(uint32_t)e.w << 32) | (uint32_t)e.z;
-                const bool in = (unsigned)(t.row + e.y) < (unsigned)t.h;
-                v[b] = t.load(t.row0 + off, in ? t.row_bytes : 0u, e.x);
-            }
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                if constexpr (FMT == KB_F32) sum.add(v[b]);
-                else sum.add(v[b], inv_scale[i0 + b].x, inv_scale[i0 + b].y);
-            }
-        }
-        finish(t.visit[q++], sum.P, sum.F, sum.count());
-    } while (q < n_vel && !full());
-    return q;
 }
 
 #define KB_BATCH_LIST(X) \
@@ -834,20 +816,12 @@ __device__ __forceinline__ void visit_velocities(
     float *scale = reinterpret_cast<float *>(words + kChunk + kChunk / 2 + kChunk / 4);
     t.scale = scale;
     t.x = x_first + lane;
-    if (FMT != KB_F32 && n_img > kMaxScaleImages) {
-        for (int v0 = part * chunk; v0 < n_vel; v0 += parts * chunk) {
-            const int end = min(v0 + chunk, n_vel);
-            for (int q = v0; q < end;) {
-                q = visit_serial<FMT>(t, inv_scale, end, q, finish, full);
-                if (full()) drain();
-            }
-        }
-        return;
-    }
     if constexpr (FMT != KB_F32) {
         // Image 1 first (0 past the last image: a gather there reads 0).
         const float *isc = reinterpret_cast<const float *>(inv_scale + 1);
-        for (int q = lane; q < kScaleWords; q += 64) scale[q] = q < 2 * n_img - 2 ? isc[q] : 0.f;
+        for (int q = lane; q < kHeldScaleWords; q += 64)
+            scale[q] = q < 2 * n_img - 2 ? isc[q] : 0.f;
+        t.more_scale = isc;
         wave_sync();
     }
     // Image 0 is the start image: its displacement is (0, 0) for every
@@ -929,8 +903,12 @@ __device__ __forceinline__ void visit_velocities(
         if (c0 == NV) q = visit_class<NV, kOne, FMT, RUNS>(t, v0, run, n, q, finish, full);  \
     }                                                                                        \
     if constexpr (NV % 2 == 0 && NV <= MAXNV && NV > MAXNV / 2) {                            \
-        if (c0 == kMulti + NV)                                                               \
-            q = visit_class<NV, kMany, FMT, RUNS>(t, v0, run, n, q, finish, full);           \
+        if (c0 == kMulti + NV) {                                                             \
+            if (FMT == KB_F32 || n_img - 1 <= kMaxScaleImages)                               \
+                q = visit_class<NV, kMany, FMT, RUNS>(t, v0, run, n, q, finish, full);       \
+            else if constexpr (FMT != KB_F32)                                                \
+                q = visit_class<NV, kManyMore, FMT, RUNS>(t, v0, run, n, q, finish, full);   \
+        }                                                                                    \
     }
                 KB_BATCH_LIST(KB_CASE)
 #undef KB_CASE

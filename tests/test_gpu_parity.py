@@ -526,6 +526,31 @@ def test_rescore_of_plain_candidates_equals_topk(torch_dev, case):
         assert np.array_equal(fg[rest].view(np.uint8), ff[rest].view(np.uint8))
 
 
+@pytest.mark.parametrize("lp", ["f16", "bf16"])
+@pytest.mark.parametrize("n,nv,k", [(65, 70, 50), (66, 40, 5), (81, 90, 64), (100, 60, 20)])
+def test_16bit_velocities_seen_in_more_images_than_the_lds_holds_scales_of(torch_dev, n, nv, k,
+                                                                           lp):
+    """Fast and slow trajectories over 65 images and more: the scales of the
+    first 64 come from the LDS, those of later ones from memory."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    s = synth.random_stack(39, n=n, h=21, w=91, n_vel=nv, k=k, psf_size=5, vmax=130.0)
+    s.vel[::2] *= 0.02
+    for i in range(n):          # (scales that differ from image to image)
+        s.img[i] *= 2.0 ** (i % 5)
+        s.var[i] *= 4.0 ** (i % 5)
+    _say(f"case many images N={n} V={nv} k={k} lp={lp}")
+    ref = oracle.search(s.img, s.var, s.mask, s.t, s.psf, s.vel, k)
+    ref["all_Sabs"] = oracle.trajectory_sums(
+        np.abs(ref["psi"]), ref["phi"], oracle.validity(s.img, s.var, s.mask),
+        oracle.displacements(s.t, s.vel))[0]
+    img, var, mask = (torch.from_numpy(a).to("cuda:0") for a in (s.img, s.var, s.mask))
+    _, src, sc = lib.make_psi_phi(img, var, mask, s.psf, lp=lp)
+    cand = lib.search(src, s.t, s.vel, k, lp_scale=sc)
+    torch.cuda.synchronize()
+    parity.check_lp_candidates(parity.to_numpy(cand), s, ref, lp, k)
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 25])
 def test_rescore_of_any_image_count_and_far_velocities(torch_dev, n):
     """Every remainder of the re-score's image groups, with velocities whose
