@@ -31,9 +31,9 @@ constexpr int TH_STRIP = 4;        // tiles per strip of the tile order
 // One tile: 64 adjacent start pixels of one row, every velocity, with the
 // top-k search's gathers (visit_velocities); each trajectory is scored and
 // appended if nu >= nu_min: one atomic per wave reserves the wave's slots.
-template <bool RUNS>
+template <bool RUNS, class Pace>
 __device__ __forceinline__ void threshold_tile(
-    uint32_t *lds, const float2 *__restrict__ planes, int n_img, int h, int w,
+    Pace &&pace, uint32_t *lds, const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, const Reach &reach, int row, int seg, float nu_min, kb_hit *__restrict__ hits,
     uint64_t cap, unsigned long long *__restrict__ n_hits) {
@@ -66,7 +66,7 @@ __device__ __forceinline__ void threshold_tile(
     };
     visit_velocities<KB_F32, TH_NV, RUNS>(lds, planes, nullptr, n_img, h, w, disp, disp_stride,
                                           vel_index, n_vel, reach, row, seg, 0, 1, kChunk, finish,
-                                          []() { return false; }, []() {}, []() {});
+                                          []() { return false; }, []() {}, pace);
 }
 
 // Strip tile order, one wave per tile.
@@ -78,40 +78,34 @@ __global__ __launch_bounds__(64) void search_threshold_kernel(
     __shared__ uint32_t lds[kVisitWords];
     int row, seg;
     strip_tile(xcd_remap((int)blockIdx.x, ntiles), nseg, h, TH_STRIP, row, seg);
-    threshold_tile<false>(lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel, reach,
-                          row, seg, nu_min, hits, cap, n_hits);
+    threshold_tile<false>([]() {}, lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel,
+                          reach, row, seg, nu_min, hits, cap, n_hits);
 }
 
 // The paced persistent order of the float32 top-k search: per generation each
 // XCD covers one block of start pixels and its waves wait (a bounded time) for
-// each other at the end of the generation, so that their gathers share the
-// XCD's L2.  The wait only shapes timing.
+// each other at the end of the generation, and inside the tiles of a long walk,
+// so that their gathers share the XCD's L2 (25 x 4096^2, 4000 velocities: 1205 ms with
+// the generation's pace alone, 685 with both, 1160 before the classes).  The wait
+// only shapes timing.
 __global__ __launch_bounds__(64) void search_threshold_persistent_kernel(
     const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
     int n_vel, Reach reach, PersistMap pm, float nu_min, kb_hit *__restrict__ hits,
     uint64_t cap, unsigned long long *__restrict__ n_hits, uint32_t *sync) {
     __shared__ uint32_t lds[kVisitWords];
-    uint32_t *xcd_count = sync + (blockIdx.x & 7);
-    const uint32_t per_xcd = gridDim.x >> 3;
-    int spin = pm.spin;
+    XcdPace xcd(sync, pm.spin);
+    auto pace = [&]() {
+        if (pm.long_walk) xcd.pace(1);
+    };
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
-        if (pm.map(gen, (int)blockIdx.x, row, seg)) {
-            threshold_tile<true>(lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel,
-                                 reach, row, seg, nu_min, hits, cap, n_hits);
-        }
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_add(xcd_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t target = (uint32_t)(gen + 1) * per_xcd;
-        int i = 0;
-        for (; i < spin; ++i) {
-            if (__hip_atomic_load(xcd_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
-                target)
-                break;
-            __builtin_amdgcn_s_sleep(8);
-        }
-        if (i == spin) spin = 0;
+        const bool ok = pm.map(gen, (int)blockIdx.x, row, seg);
+        if (ok)
+            threshold_tile<true>(pace, lds, planes, n_img, h, w, disp, disp_stride, vel_index,
+                                 n_vel, reach, row, seg, nu_min, hits, cap, n_hits);
+        // Generation boundary.
+        xcd.pace(ok || !pm.long_walk ? 1 : 1 + paces_inside(n_vel));
     }
 }
 
@@ -464,7 +458,7 @@ kb_status launch_threshold(const float *psi_phi, int64_t n_img, int64_t h, int64
         pm.nbr = ((int)h + pm.brows - 1) / pm.brows;
         pm.generations = block_generations(pm.nbc, pm.nbr);
         pm.spin = KBMI_PERSIST_SPIN;
-        pm.long_walk = 0;
+        pm.long_walk = is_long_walk(n_img, n_vel, true);
         uint32_t *sync = reinterpret_cast<uint32_t *>(ws + lay.sync);
         hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, sync, 8);
         kb_status st = launch_status("zero_words_kernel");

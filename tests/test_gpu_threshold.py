@@ -102,6 +102,36 @@ def test_threshold_scores_equal_topk_scores(torch_dev):
         assert no[r["y"], r["x"], slot] == r["nobs"]
 
 
+def test_threshold_long_walk_paced_inside_tiles(torch_dev):
+    """More than 17 images and 2048 velocities on a frame of several
+    generations, ragged on both sides: the hits of two searches of half the
+    velocities, which pace no tile inside."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    dev = torch.device("cuda:0")
+    n, h, w, nv, cap = 18, 131, 4099, 2150, 1 << 21
+    s = synth.random_stack(98, n=n, h=h, w=w, n_vel=nv, k=4, psf_size=5, vmax=200.0)
+    _say("case threshold long walk")
+    planes = lib.make_psi_phi(*(torch.from_numpy(a).to(dev) for a in (s.img, s.var, s.mask)),
+                              s.psf)
+
+    def hits(first, last):
+        buf = lib.alloc_hits(cap, dev)
+        count = int(lib.search_threshold(planes, s.t, s.vel[first:last], 4.5, buf))
+        assert 0 < count <= cap
+        found = buf[:count].clone()
+        found[:, 2] += first
+        found[:, 5] &= 0xFFFF
+        return found
+
+    def ordered(found):
+        key = (found[:, 1].to(torch.int64) * w + found[:, 0]) * nv + found[:, 2]
+        return found[torch.argsort(key)]
+    got, half = hits(0, nv), nv // 2
+    want = torch.cat([hits(0, half), hits(half, nv)])
+    assert torch.equal(ordered(got), ordered(want))
+
+
 def test_threshold_overflow_counts_everything(torch_dev):
     s = synth.small_stack()
     _, _, n_all, h_all = _gpu_threshold(torch_dev, s, 4.0)
