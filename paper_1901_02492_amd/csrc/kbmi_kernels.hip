@@ -51,11 +51,16 @@ constexpr int PP_TW = 64;       // output tile width
 constexpr int PP_TH = 16;       // output tile height for each row that a thread produces
 constexpr int PP_THREADS = 256; // 4 waves; each thread produces 4 columns of 1 or 2 rows
 constexpr int PP_BATCH = 4;     // staged pixels whose loads are in flight together
-// 64 x 32 tiles from which on a thread takes two rows: 20 x 2048^2 at 11 x 11 (40960
-// tiles) 1.150 -> 0.997 ms with the half-precision copy; 15 x 1024^2 at 15 x 15
-// (7680) 0.273 -> 0.278 and 20 x 512^2 at 11 x 11 (2560) 50.8 -> 57.6 us, where
-// the last round of fewer, longer workgroups leaves CUs idle.
-constexpr int64_t PP_MIN_TILES2 = 16384;
+// A thread takes two rows where a 16-bit copy is wanted, the PSF is at most 13 wide
+// and there are 1024 tiles of 64 x 32 or more.  What it gains is half the atomics on
+// the images' largest values; without them, and with wider PSFs, the larger
+// tile's LDS leaves fewer workgroups to a CU and costs more than its smaller halo
+// saves.  One row / two, ms: 15 x 2048^2 with the f16 copy 5 x 5 0.829 / 0.587, 11 x 11
+// 0.926 / 0.749, 13 x 13 0.953 / 0.864, 15 x 15 1.030 / 1.102; without a copy 5 x 5
+// 0.354 / 0.355, 11 x 11 0.561 / 0.607, 25 x 25 2.01 / 2.24.  10 x 512^2 (1280 tiles),
+// 11 x 11, f16 69 / 56 us; 5 x 256^2 (160) 31 / 34.
+constexpr int64_t PP_MIN_TILES2 = 1024;
+constexpr int PP_MAX_W2 = 13;
 // LDS of one tile with its halo for a PSF of ph rows and PW columns: the
 // (a, w) pairs, then the validity bytes (sized at launch, so a small PSF
 // leaves room for more resident workgroups).
@@ -98,13 +103,11 @@ __device__ inline void divide_by_variance(float im, float vr, bool good, float &
 // by row, left to right.
 //
 // FP32 issue bounds it (242 FMAs a pixel at 11 x 11: 0.52 ms for 20 x 2048^2).
-// Beside them, two rows a thread stage 1.5 pixels per output pixel where one
-// row stages 1.9 and reads each segment for one row only, the two divisions
-// share a reciprocal, and four staged pixels' loads are in flight together.
-// 20 x 2048^2, 11 x 11, with the half-precision copy (0.23 ms of it): 1.210 -> 0.997
-// ms; 15 x 1024^2, 15 x 15, bfloat16 copy 0.283 -> 0.273; 20 x 512^2, 11 x 11 55.5
-// -> 50.8 us.  (Squared taps from the host, a second row of scalar loads
-// beside each row of taps: 1.117 ms.)
+// Beside them, the two divisions share a reciprocal, and four staged pixels'
+// loads are in flight together: 15 x 2048^2, 11 x 11 0.628 -> 0.561 ms, 20 x 2048^2
+// 0.832 -> 0.739; with the half-precision copy and two rows a thread 1.217 -> 0.989.
+// (Squared taps from the host, a second row of scalar loads beside each row of
+// taps: 1.117 ms.)
 template <int PW, int ROWS>
 __global__ __launch_bounds__(PP_THREADS) void psi_phi_kernel(
     const float *__restrict__ img, const float *__restrict__ var,
@@ -889,7 +892,8 @@ kb_status kb_make_psi_phi(const float *img, const float *var, const uint8_t *mas
     PsfTaps taps{};
     for (int64_t u = 0; u < psf_h * psf_w; ++u) taps.t[u] = psf[u];
     const int64_t tiles_x = (w + PP_TW - 1) / PP_TW, tiles_y2 = (h + 2 * PP_TH - 1) / (2 * PP_TH);
-    const bool two = tiles_x * tiles_y2 * n_img >= PP_MIN_TILES2;
+    const bool two = lp_dtype != KB_F32 && psf_w <= PP_MAX_W2 &&
+                     tiles_x * tiles_y2 * n_img >= PP_MIN_TILES2;
     const dim3 grid((unsigned)tiles_x, (unsigned)(two ? tiles_y2 : (h + PP_TH - 1) / PP_TH),
                     (unsigned)n_img);
     hipStream_t s = (hipStream_t)stream;
@@ -905,7 +909,8 @@ kb_status kb_make_psi_phi(const float *img, const float *var, const uint8_t *mas
     switch (psf_w) {
 #define KB_PSF_W(PW)                                                                         \
     case PW:                                                                                 \
-        hipLaunchKernelGGL((two ? psi_phi_kernel<PW, 2> : psi_phi_kernel<PW, 1>), grid,       \
+        hipLaunchKernelGGL((two ? psi_phi_kernel<PW, (PW <= PP_MAX_W2 ? 2 : 1)>              \
+                                : psi_phi_kernel<PW, 1>), grid,                             \
                            dim3(PP_THREADS), psi_phi_lds_bytes<PW>((int)psf_h, two ? 2 : 1),  \
                            s, img, var, mask, (int)h, (int)w, (int)psf_h, taps, pp, maxabs);  \
         break;

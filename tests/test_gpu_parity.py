@@ -817,6 +817,32 @@ def test_planes_do_not_depend_on_the_tile_height(torch_dev, psf_shape):
         assert one.tobytes() == got[i:i + 1].tobytes()
 
 
+@pytest.mark.parametrize("lp", ["f16", "bf16"])
+@pytest.mark.parametrize("psf_shape", [(1, 1), (5, 3), (11, 11), (25, 13), (9, 15)])
+def test_planes_and_their_copy_do_not_depend_on_the_tile_height(torch_dev, psf_shape, lp):
+    """With a 16-bit copy a stack of 1024 tiles takes two rows a thread (PSFs up to
+    13 wide): planes, copy and scales of every image bit for bit what it gives
+    alone, on frames whose last tile row has one or both of a thread's rows."""
+    from paper_1901_02492_amd import lib
+    torch = torch_dev
+    rng = np.random.default_rng(92)
+    dev = torch.device("cuda:0")
+    psf = rng.uniform(0.0, 1.0, psf_shape).astype(np.float32)
+    for n, h, w in ((40, 97, 387), (40, 98, 449)):    # 1120 and 1280 tiles of 64 x 32
+        img = rng.standard_normal((n, h, w)).astype(np.float32)
+        img *= 2.0 ** rng.integers(-3, 4, (n, 1, 1))
+        var = rng.uniform(0.5, 2.0, (n, h, w)).astype(np.float32)
+        mask = (rng.random((n, h, w)) < 0.02).astype(np.uint8)
+        _say(f"case tile height psf={psf_shape} {n}x{h}x{w} {lp}")
+        d = [torch.from_numpy(a).to(dev) for a in (img, var, mask)]
+        got = lib.make_psi_phi(*d, psf, lp=lp)
+        for i in range(0, n, 13):
+            one = lib.make_psi_phi(*(a[i:i + 1].contiguous() for a in d), psf, lp=lp)
+            for a, b in zip(got, one):
+                assert torch.equal(a[i:i + 1].contiguous().view(torch.uint8),
+                                   b.contiguous().view(torch.uint8))
+
+
 @pytest.mark.parametrize("lp", [None, "bf16"])
 @pytest.mark.parametrize("k", [1, 5, 16, 27, 50, 64])
 @pytest.mark.parametrize("h", [20, 290, 700])
