@@ -427,7 +427,9 @@ ClusterLayout cluster_layout(int64_t n_hits, int64_t n_vel) {
     l.parent = 0;
     l.best_nu = l.parent + r256(n * sizeof(int32_t));
     l.best_key = l.best_nu + r256(n * sizeof(uint32_t));
-    l.rep_of_root = l.best_key + r256(n * sizeof(uint64_t));
+    // (best_key's space holds the bitmap first.)
+    l.rep_of_root = l.best_key + r256(std::max<uint64_t>(n * sizeof(uint64_t),
+                                                         l.slots / CL_SLOTS_PER_WORD * 8));
     l.vel = l.rep_of_root + r256(n * sizeof(int32_t));
     l.next = l.vel + r256(static_cast<size_t>(n_vel) * 2 * sizeof(double));
     l.table_key = l.next + r256(n * sizeof(int32_t));
@@ -567,8 +569,7 @@ kb_status kb_cluster_hits(const kb_hit *hits, int64_t n_hits, const double *vel,
     // of side 1; only identical hits join).
     const double side = eps > 0.0 ? eps * (1.0 + 0x1p-20) : 1.0;
     const double inv_c = 1.0 / side;
-    // The bitmap lies in best_key's space, which is written after its last use
-    // (slots <= max(4 n, 64) words of half a byte a slot; best_key has 8 n).
+    // The bitmap lies in best_key's space, which is written after its last use.
     uint64_t *bitmap = best_key;
     hipLaunchKernelGGL(cl_init_kernel,
                        dim3((unsigned)std::min<uint64_t>(2048, (lay.slots + 255) / 256)),

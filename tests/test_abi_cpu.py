@@ -315,3 +315,19 @@ def test_every_batch_fits_a_launch(tmp_path):
                     os.path.join(ROOT, "tests", "batch_grid_check.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 31, 32, 33, 64, 65, 1000, 4096, 100_001])
+def test_cluster_workspace_holds_the_bitmap(n):
+    """Half a byte of bitmap a table slot (64 slots at least, twice the hits and
+    more) beside parent, best nu, best key, representative and list of every
+    hit, velocities, and 12 bytes a slot; and no more than that."""
+    slots = 64
+    while slots < 2 * n:
+        slots *= 2
+
+    def r256(b):
+        return (b + 255) // 256 * 256
+    want = 4 * r256(4 * n) + r256(max(8 * n, slots // 2)) + r256(16 * 7) + r256(8 * slots) + \
+        r256(4 * slots)
+    assert lib.load().kb_cluster_workspace_bytes(n, 7) == want
