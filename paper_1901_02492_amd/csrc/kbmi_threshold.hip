@@ -31,12 +31,12 @@ constexpr int TH_STRIP = 4;        // tiles per strip of the tile order
 // One tile: 64 adjacent start pixels of one row, every velocity, with the
 // top-k search's gathers (visit_velocities); each trajectory is scored and
 // appended if nu >= nu_min: one atomic per wave reserves the wave's slots.
-template <bool RUNS, class Pace>
+template <class Pace>
 __device__ __forceinline__ void threshold_tile(
     Pace &&pace, uint32_t *lds, const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
-    int n_vel, const Reach &reach, int row, int seg, float nu_min, kb_hit *__restrict__ hits,
-    uint64_t cap, unsigned long long *__restrict__ n_hits) {
+    int n_vel, int row, int seg, float nu_min, kb_hit *__restrict__ hits, uint64_t cap,
+    unsigned long long *__restrict__ n_hits) {
     const int lane = (int)threadIdx.x;
     const int x0 = seg * 64 + lane;
     const uint64_t below = (uint64_t(1) << lane) - 1;
@@ -64,22 +64,24 @@ __device__ __forceinline__ void threshold_tile(
             }
         }
     };
-    visit_velocities<KB_F32, TH_NV, RUNS>(lds, planes, nullptr, n_img, h, w, disp, disp_stride,
-                                          vel_index, n_vel, reach, row, seg, 0, 1, kChunk, finish,
-                                          []() { return false; }, []() {}, pace);
+    // (Without runs: they gain 4 to 9 % up to 8 images, but with more of them tiles
+    // inside run ahead of their XCD's others, 15 x 4096^2, 240 velocities 31.3 -> 35.1 ms.)
+    visit_velocities<KB_F32, TH_NV, false>(lds, planes, nullptr, n_img, h, w, disp, disp_stride,
+                                           vel_index, n_vel, Reach{}, row, seg, 0, 1, kChunk,
+                                           finish, []() { return false; }, []() {}, pace);
 }
 
 // Strip tile order, one wave per tile.
 __global__ __launch_bounds__(64) void search_threshold_kernel(
     const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
-    int n_vel, Reach reach, int nseg, int ntiles, float nu_min, kb_hit *__restrict__ hits,
-    uint64_t cap, unsigned long long *__restrict__ n_hits) {
+    int n_vel, int nseg, int ntiles, float nu_min, kb_hit *__restrict__ hits, uint64_t cap,
+    unsigned long long *__restrict__ n_hits) {
     __shared__ uint32_t lds[kVisitWords];
     int row, seg;
     strip_tile(xcd_remap((int)blockIdx.x, ntiles), nseg, h, TH_STRIP, row, seg);
-    threshold_tile<false>([]() {}, lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel,
-                          reach, row, seg, nu_min, hits, cap, n_hits);
+    threshold_tile([]() {}, lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel, row,
+                   seg, nu_min, hits, cap, n_hits);
 }
 
 // The paced persistent order of the float32 top-k search: per generation each
@@ -88,24 +90,25 @@ __global__ __launch_bounds__(64) void search_threshold_kernel(
 // so that their gathers share the XCD's L2 (25 x 4096^2, 4000 velocities: 1205 ms with
 // the generation's pace alone, 685 with both, 1160 before the classes).  The wait
 // only shapes timing.
+template <bool LONG>
 __global__ __launch_bounds__(64) void search_threshold_persistent_kernel(
     const float2 *__restrict__ planes, int n_img, int h, int w,
     const GatherEntry *__restrict__ disp, int disp_stride, const int32_t *__restrict__ vel_index,
-    int n_vel, Reach reach, PersistMap pm, float nu_min, kb_hit *__restrict__ hits,
-    uint64_t cap, unsigned long long *__restrict__ n_hits, uint32_t *sync) {
+    int n_vel, PersistMap pm, float nu_min, kb_hit *__restrict__ hits, uint64_t cap,
+    unsigned long long *__restrict__ n_hits, uint32_t *sync) {
     __shared__ uint32_t lds[kVisitWords];
     XcdPace xcd(sync, pm.spin);
     auto pace = [&]() {
-        if (pm.long_walk) xcd.pace(1);
+        if constexpr (LONG) xcd.pace(1);
     };
     for (int gen = 0; gen < pm.generations; ++gen) {
         int row, seg;
         const bool ok = pm.map(gen, (int)blockIdx.x, row, seg);
         if (ok)
-            threshold_tile<true>(pace, lds, planes, n_img, h, w, disp, disp_stride, vel_index,
-                                 n_vel, reach, row, seg, nu_min, hits, cap, n_hits);
+            threshold_tile(pace, lds, planes, n_img, h, w, disp, disp_stride, vel_index, n_vel,
+                           row, seg, nu_min, hits, cap, n_hits);
         // Generation boundary.
-        xcd.pace(ok || !pm.long_walk ? 1 : 1 + paces_inside(n_vel));
+        xcd.pace(ok || !LONG ? 1 : 1 + paces_inside(n_vel));
     }
 }
 
@@ -116,7 +119,7 @@ int threshold_grid() {
     if (cached[dev] == 0) {
         int per_cu = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, search_threshold_persistent_kernel, 64, 0) != hipSuccess ||
+                &per_cu, search_threshold_persistent_kernel<false>, 64, 0) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
         // (12 and 16 workgroups a CU, which the registers allow, take 19.9 and 19.7 ms
@@ -439,8 +442,8 @@ ClusterLayout cluster_layout(int64_t n_hits, int64_t n_vel) {
 }
 
 kb_status launch_threshold(const float *psi_phi, int64_t n_img, int64_t h, int64_t w,
-                           int64_t n_vel, const Reach &reach, float nu_min, kb_hit *hits,
-                           int64_t max_hits, uint64_t *n_hits, void *workspace, hipStream_t s) {
+                           int64_t n_vel, float nu_min, kb_hit *hits, int64_t max_hits,
+                           uint64_t *n_hits, void *workspace, hipStream_t s) {
     char *ws = static_cast<char *>(workspace);
     const WorkspaceLayout lay = workspace_layout(n_img, h, w, n_vel);
     const int nseg = (int)((w + 63) / 64);
@@ -465,16 +468,18 @@ kb_status launch_threshold(const float *psi_phi, int64_t n_img, int64_t h, int64
         hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, sync, 8);
         kb_status st = launch_status("zero_words_kernel");
         if (st != KB_OK) return st;
-        hipLaunchKernelGGL(search_threshold_persistent_kernel, dim3((unsigned)grid), dim3(64),
-                           0, s, reinterpret_cast<const float2 *>(psi_phi), (int)n_img, (int)h,
-                           (int)w, disp, (int)table_stride(n_img), order, (int)n_vel, reach, pm,
-                           nu_min, hits, (uint64_t)max_hits,
-                           reinterpret_cast<unsigned long long *>(n_hits), sync);
+        hipLaunchKernelGGL((pm.long_walk ? search_threshold_persistent_kernel<true>
+                                         : search_threshold_persistent_kernel<false>),
+                           dim3((unsigned)grid), dim3(64), 0, s,
+                           reinterpret_cast<const float2 *>(psi_phi), (int)n_img, (int)h, (int)w,
+                           disp, (int)table_stride(n_img), order, (int)n_vel, pm, nu_min, hits,
+                           (uint64_t)max_hits, reinterpret_cast<unsigned long long *>(n_hits),
+                           sync);
         return launch_status("search_threshold_persistent_kernel");
     }
     hipLaunchKernelGGL(search_threshold_kernel, dim3((unsigned)ntiles), dim3(64), 0, s,
                        reinterpret_cast<const float2 *>(psi_phi), (int)n_img, (int)h, (int)w,
-                       disp, (int)table_stride(n_img), order, (int)n_vel, reach, nseg, (int)ntiles,
+                       disp, (int)table_stride(n_img), order, (int)n_vel, nseg, (int)ntiles,
                        nu_min, hits, (uint64_t)max_hits,
                        reinterpret_cast<unsigned long long *>(n_hits));
     return launch_status("search_threshold_kernel");
@@ -518,8 +523,8 @@ kb_status kb_search_threshold(const float *psi_phi, int64_t n_img, int64_t h, in
                        reinterpret_cast<unsigned long long *>(n_hits));
     st = launch_status("zero_u64_kernel");
     if (st != KB_OK) return st;
-    return launch_threshold(psi_phi, n_img, h, w, n_vel, reach_of(t, n_img, vel, n_vel, h, w),
-                            nu_min, hits, max_hits, n_hits, workspace, s);
+    return launch_threshold(psi_phi, n_img, h, w, n_vel, nu_min, hits, max_hits, n_hits,
+                            workspace, s);
 }
 
 size_t kb_cluster_workspace_bytes(int64_t n_hits, int64_t n_vel) {
