@@ -409,10 +409,10 @@ size_t kb_search_batch_workspace_bytes(const kb_job *jobs, int64_t n_jobs);
  * kb_search_batch - kb_search for several stacks in one launch, whatever
  * their image counts (the serving path: small stacks share the GPU instead
  * of each under-filling it).  Its work items are the jobs' start-pixel tiles,
- * tile after tile, those of the longest tiles first; a job of float32
- * planes large enough for kb_search's paced block order comes before them
- * and keeps that order.  All jobs share `dtype` and
- * `k_cand`.  Each job's candidates are exactly what kb_search would write
+ * tile after tile, those of the longest tiles first; a job that kb_search
+ * would walk in its paced block order (large frames of float32 planes, and of
+ * 16-bit planes with many images, velocities and candidates) comes before them
+ * and keeps that order.  All jobs share `dtype` and `k_cand`.  Each job's candidates are exactly what kb_search would write
  * for it alone (same arithmetic, same order), whatever else is in the batch.
  *   jobs       host array of n_jobs (1 <= n_jobs <= 4096) descriptors; read
  *              before return.

@@ -97,7 +97,7 @@ struct BatchShape {
 
 // Waves of a search kernel per SIMD.  16-bit planes take as many as a short list
 // leaves registers for, two batches of 16 loads and 16 images' scales beside it
-// (12 x 2048^2 f16, 600 velocities, K = 5 11.7 ms with 2 waves, 8.3 with 3, 7.1 with 4).
+// (12 x 2048^2 f16, 600 velocities, K = 5 11.6 ms with 2 waves, 8.3 with 3, 7.0 with 4).
 // One more spills: K = 10 with 4 waves 11.3 ms for 8.7 with 3, in bfloat16, whose
 // values take two registers more to widen, 15.1 for 9.4.
 // Float32 planes, whose gathers keep the memory path busy with two, lose as
@@ -522,8 +522,13 @@ constexpr int kChunk = 256;           // velocities classified at once
 // pace alone, 714 with one every 1024 velocities too (903 without classes, in
 // step by themselves); 25 x 2048 x 4096, 3000 velocities 284 -> 266.  Fewer images
 // lose by the waiting (13 x 1024^2, 32000 velocities, every 512: 186 -> 228).
-// 16-bit planes walk in the paced order then: 25 x 1024 x 2048, 4000 velocities
-// 73.8 -> 65.9 ms, 25 x 4096^2 757 -> 608, 25 x 2048 x 4096, 3000 velocities 272 -> 228.
+// 16-bit planes with lists for two waves a SIMD walk in the paced order then:
+// 25 x 1024 x 2048, 4000 velocities 73.8 -> 65.9 ms, 25 x 4096^2 757 -> 608, 25 x 2048 x 4096,
+// 3000 velocities 272 -> 228.  The line lies at 18 images; K = 50, unpaced / paced:
+// 2048^2, 4000 velocities, float32 17 images 115 / 119 ms, 18 134 / 136, 20 138 / 138, 25
+// 163 / 158; f16 15 images 72 / 84, 18 130 / 128; 25 x 4096^2 f16, 2400 velocities 423 / 387.
+// Shorter 16-bit lists, with more waves, lose by that order: 20 x 2048^2 f16, 4000
+// velocities, K = 20 97 / 148, K = 10 99 / 146.
 constexpr int kPaceVelocities = 1024;
 static_assert(kPaceVelocities % kChunk == 0, "a pace stands between two chunks");
 constexpr int kMaxScaleImages = 64;   // 16-bit planes: images whose inverse scales lie in the LDS
@@ -777,7 +782,7 @@ __device__ __forceinline__ int visit_class(const Tile<FMT> &t, int v0, uint32_t 
 // a frame whose edges cut trajectories has half the classes to begin anew, but
 // for the velocities that all of up to 8 images see: on large frames these are
 // most, and a load in 8 is worth it (8 x 4096^2 float32, 600 velocities, K = 5 49.5 ->
-// 46.5 ms; exact classes throughout: 12 x 300^2 0.410 -> 0.427 ms).
+// 46.5 ms; exact classes throughout: 12 x 300^2, K = 5 0.421 -> 0.437 ms).
 constexpr int kMulti = 15;
 template <int MAXNV>
 __device__ inline int class_of(int m, int all) {
@@ -838,7 +843,7 @@ __device__ __forceinline__ void visit_velocities(
     // lane reads a line of its own.  (16-bit planes and large float32 frames, with
     // lists that leave registers for it: 15 x 2048^2 f16, 600 velocities, K = 10 9.95 -> 9.3
     // ms; 8 x 2048^2 float32, K = 1 12.2 -> 11.2.  Small float32 frames have few such
-    // tiles and lose 2 % by the question: 12 x 251 x 301, K = 5.)
+    // tiles and lose 1 to 2 % by the question: 12 x 251 x 301, K = 5.)
     const bool inside = RUNS && ni > 0 && row + reach.y_lo >= 0 && row + reach.y_hi < h &&
                         x_last + reach.x_lo >= 0 && x_first + reach.x_hi < w;
     const uint32_t run = inside ? (uint32_t)ni << 16 : 0u;

@@ -1019,10 +1019,10 @@ kb_status kb_topk(const float *psi_phi_f32, int64_t n_img, int64_t h, int64_t w,
 
 namespace {
 
-// Batch workspace: the device job descriptors (in launch order: the jobs of
-// image-count class 0, then 1, then 2), the per-XCD counters of the three
-// launches (3 x 8 words), then per job its table, visiting order and 16-bit
-// inverse scales (each 256-byte aligned; job order as given).
+// Batch workspace: the device job descriptors (in launch order: the jobs in
+// block order, then the others, those of the longest tiles first), the per-XCD
+// counters (8 words), then per job its table, visiting order and 16-bit inverse
+// scales (each 256-byte aligned; job order as given).
 struct BatchLayout {
     std::vector<size_t> table, order, inv_scale;
     size_t sync, total;
