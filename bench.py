@@ -62,6 +62,18 @@ def measured_traffic():
         return None
 
 
+def seen_images(lib, s, h, w):
+    """Images beside image 0 that a tile (64 start pixels of a row) sees of one
+    velocity's trajectories, on average over tiles and velocities."""
+    d = lib.displacements(s.t, s.vel)[:, 1:].astype(np.int64)
+    dx, dy = d[..., 0], d[..., 1]
+    nseg = (w + 63) // 64
+    right = np.clip((w - dx + 63) // 64, 0, nseg)              # tiles that begin left of w - dx
+    left = np.where(-dx < w, np.minimum(np.maximum(-dx, 0) // 64, nseg), nseg)
+    tiles = np.maximum(right - left, 0) * np.maximum(h - np.abs(dy), 0)
+    return float(tiles.sum() / (d.shape[0] * nseg * h))
+
+
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
@@ -375,10 +387,10 @@ def main():
                                f"waves per SIMD and 16/32 loads in flight",
                 "peak_2wave_per_simd": peak["l2_2wave_gbs"],
                 "frac_of_2wave_peak": achieved / peak["l2_2wave_gbs"],
-                # image 0 sits at displacement (0, 0) for every velocity and is
-                # loaded once per start pixel: the kernel issues (N - 1) / N of
-                # the algorithmic gathers
-                "issued_frac": achieved * (n - 1) / n / peak["l2_gbs"],
+                # of the algorithmic gathers the kernel issues those of the images
+                # that a tile's trajectories see (image 0, at displacement (0, 0)
+                # for every velocity, once per start pixel)
+                "issued_frac": achieved * seen_images(lib, s, h, w) / n / peak["l2_gbs"],
                 "hbm_gather_peak": peak["hbm_gather_gbs"],
                 "hbm": {"achieved": hbm_gbs, "peak": HBM_PEAK_GBS,
                         "frac": None if hbm_gbs is None else hbm_gbs / HBM_PEAK_GBS,
